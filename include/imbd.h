@@ -259,7 +259,7 @@ enum imbd_option {
     IMBD_OPT_GEMM_SPLITS = 9,   /* K split of the tiled template, 0 = planned */
     IMBD_OPT_CONV_NT = 10,      /* 0: the conv tile on the tiled template; 1: on the large-tile
                                    kernels, tile height planned (default); 2 / 3: with tiles of
-                                   128 / 112 output positions */
+                                   at most 128 / 112 output positions */
     IMBD_OPT_SKINNY_NB = 11,    /* samples per workgroup of the B <= 256 product kernel, in units
                                    of 64 (1, 2 or 4), 0 = planned */
     IMBD_OPT_DW_WIDE_DUAL = 12, /* the large-tile fused update with two workgroups per CU

@@ -1,7 +1,7 @@
 // Forward and input-gradient passes of the domain-parallel 3x3 conv tile (Sec. 2.2, pure
 // domain parallelism: each process convolves its spatial tile with the halo supplied;
-// the input gradient takes the output gradient with its own halo), for 256 output
-// channels, as implicit GEMMs on the zero-padded (H+2) x (W+2) grid:
+// the input gradient takes the output gradient with its own halo), for channel counts that
+// are multiples of 64, as implicit GEMMs on the zero-padded (H+2) x (W+2) grid:
 //   forward   D(P, o) = sum_{tap, c} x_pad[P + r*(W+2) + s][c] * W[o][tap][c]
 //   input grad D(P, c) = sum_{tap, o} dy_pad[P + (2-r)*(W+2) + 2-s][o] * W[o][tap][c]
 // with tap = 3r + s and P = (n (H+2) + h) (W+2) + w the row of the padded grid whose
@@ -9,320 +9,438 @@
 // [positions][channels] matrix, so a k-slab (64 channels of one tap) of the activation
 // operand is 64 contiguous channels of shifted rows.
 //
-// The products are MFMA-bound (2 x 9 x C flops per output), so a workgroup owns a large
-// tile: 128 (or 112) output positions x all 256 channels over the whole K = 9 C (no split,
-// no partials; the epilogue writes the outputs). With one workgroup per CU, the tiles of a
-// short last round run as two 128-channel halves each (the loader and MMA waves of the
-// other half only keep the slab barriers). The kernel keeps the layout of the skinny-batch
-// kernel (csrc/skinny.hip): both operands travel through LDS in 64-k slabs written by
-// buffer loads that go straight to LDS in whole 128-byte lines, loader waves with their
-// own memory counters, one barrier per slab, XOR-swizzled 16-byte chunks:
-//  * waves 8-9 stream the activation slab (128 or 112 shifted rows x 128 B) through a
-//    4-slot ring;
-//  * waves 10-11 stream the weight slab (256 channels x 64 k) through a 3-slot ring: rows
-//    of W for the forward pass, k-rows of W (64 output channels of one tap x 256 input
-//    channels, as four 64-channel quarters) for the input gradient, whose fragments then
-//    come from the gfx950 LDS transpose read;
-//  * waves 0-7, two per SIMD, each accumulate 64 (or 48) positions x 64 channels in
-//    registers.
-// After the last slab the tile goes through LDS ([position][channel], fp32) and is written
-// as whole 512-byte (bf16) or 1 KB (fp32) output rows.
+// What bounds it: with every byte loaded into LDS once per tap, a slab of 128 positions x
+// 256 channels (48 KB) took 0.56 us for the loads alone, 0.54 us for the MFMAs with their
+// fragment reads and 0.78 us for both, and each round of one-tile workgroups lost 6 us to
+// its first loads and its write-out. So the three taps of one kernel row share one
+// activation slab: per image row that the tile touches, its positions and the two columns
+// after them (16-20% more rows than positions instead of three times as many; the loads of
+// as many MFMAs then take 0.34 us); a tap is a shift of the fragment reads. And a workgroup
+// walks through several tiles: its loaders run ahead into the next tile while the tile
+// before is written from registers. What is left at 256 x 128 is power: a slab takes 0.58
+// us on zeros and 0.76 us on normally distributed data (1.3 PFLOP/s, what a large library
+// product reaches on the same card). Measured (forward / input gradient, us, before ->
+// after; the other channel counts were on the tiled GEMM template):
+//   32 x 56 x 56, 256 -> 256:  117 / 110 -> 106 / 107
+//   64 x 13 x 13, 384 -> 384:   80 / 105 -> 27.6 / 29.6
+//   32 x 56 x 56,  64 -> 128:   49 /  79 -> 21.2 / 23.2
+//   32 x 14 x 14, 512 -> 512:   80 / 127 -> 33.6 / 35.2
+//    8 x  7 x  7, 512 -> 512:   71 / 121 -> 18.5 / 19.8
+//
+// Work split: the positions, in blocks of 16, are dealt out evenly to 256 / (channel
+// tiles) workgroups per channel tile, and each cuts its share into tiles of nearly equal
+// height, so that no short last round of tiles remains. Eight MMA waves (two per SIMD)
+// hold 64 positions x 64 channels each, laid out as WP position groups x WC channel groups
+// x WK halves of each slab's k:
+//   WP = 4, WC = 2: up to 256 positions x 128 channels (shares of more than 128 positions);
+//   WP = 2, WC = 2, WK = 2: up to 128 positions x 128 channels: small grids, where shares
+//     of 128 positions are all there is; the two k halves keep both waves of a SIMD busy
+//     at 64 x 64 fragments each and are added through LDS at the end of a tile;
+//   WP = 4, WC = 1, WK = 2: up to 256 positions x 64 channels, for 64 output channels.
+// A channel count that is no multiple of 128 leaves half of its last tile's waves idle.
+//
+// Both operands travel through LDS in 64-k slabs written by buffer loads that go straight
+// to LDS in whole 128-byte lines, XOR-swizzled in 16-byte chunks; one barrier per slab:
+//  * waves 8-9 stream the activation slabs (one per kernel row and 64-channel chunk)
+//    through two slots, a whole slab ahead;
+//  * waves 10-11 stream the weight slabs (BN channels x 64 k of one tap) through five
+//    slots: rows of W for the forward pass, k-rows of W (64 output channels of one tap x
+//    BN input channels, in 64-channel quarters) for the input gradient, whose fragments
+//    then come from the gfx950 LDS transpose read.
+// Fragments are read between the MFMAs of the k-step before, block by block in place
+// (activations) or into a second set (weights); reads stay in flight over the slab barrier,
+// so the weight loaders keep one slot more of distance. With all reads ahead of the MFMAs
+// and waited for at every barrier, the small-grid layout spilled registers and took 0.54
+// instead of 0.41 us a slab (64 x 13 x 13, 384 channels: 36.8 instead of 27.6 us).
+// The weights are the MFMA's row operand, so a lane's four sums are four consecutive
+// channels of one position; a lane exchange makes them eight, and each store instruction
+// writes 64-byte runs.
 
-#include <stdlib.h>
+#include <algorithm>
 
 #include "cdna4.h"
 
 namespace imbd {
 namespace {
 
-constexpr int CV_BM = 128;             // positions per workgroup (at most; 112 with FM = 7)
-constexpr int CV_BN = 256;             // channels of the output per workgroup
-constexpr int CV_KS = 64;              // k per slab: 64 channels of one tap
-constexpr int CV_NA = 4;               // activation ring slots
-constexpr int CV_NW = 3;               // weight ring slots
-constexpr int CV_WSLOT = CV_BN * 128;  // 32 KB
+constexpr int CV_NW = 5;               // weight ring slots
 constexpr int CV_QSLOT = 64 * 128;     // one 64-channel quarter of a transposed weight slab
-constexpr int CV_PITCH = CV_BN + 4;    // staging row pitch in floats (1040 B)
-constexpr int CV_CUS = 256;            // compute units of the chip: one workgroup each per round
+constexpr int CV_CUS = 256;            // compute units of the chip: one workgroup each
+constexpr int CV_XBUF = 32 * 1024;     // exchange of the two k halves' sums
 
 struct CvArgs {
   const uint16_t *act;  // x_pad (forward) or dy_pad (input gradient): [N][H+2][W+2][Ck]
   const uint16_t *w;    // [C_out][3][3][C_in]
-  void *out;            // [N][H][W][256]
+  void *out;            // [N][H][W][Cn]
   int out_bf16;
-  int N, H, W, Ck, Cw;  // Ck: channels of act (the reduction); Cw: C_in (the W row's channel stride)
-  int M, tiles;         // output positions N*H*W, tiles of 128 of them
-  int tfull, gfull;     // tiles run whole (the first tfull), their workgroups (a multiple of 8)
+  int N, H, W;
+  int Ck, Cn, Ci;       // channels of act (the reduction), of out, and C_in (W's channel stride)
+  int64_t w_bytes;
+  int M, nblk;          // output positions N*H*W, blocks of 16 of them
+  int nct, groups;      // channel tiles; workgroups (shares of the blocks) per channel tile
+  int tmax;             // position blocks per tile at most
 };
+
+// Rows of an activation slab in LDS: the image rows' pieces of the tile one after another,
+// each with two columns more than the tile has positions in it.
+constexpr int cv_slab_rows(int wp) { return wp == 4 ? 304 : 160; }
 
 __device__ __forceinline__ int cv_swz_kc(int r) { return r & 7; }
 __device__ __forceinline__ int cv_swz_tr(int r) { return 2 * ((r >> 1) & 1) + 4 * ((r >> 3) & 1); }
+template <int V>
+struct CvInt {
+  static constexpr int value = V;
+};
+// x / d for 0 <= x < 2^16 (inv = 1 / d): the half keeps the quotient's error away from whole numbers
+__device__ __forceinline__ int cv_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
-// TR: input gradient (W read transposed); else forward. FM: 16-position blocks per tile
-// (8: 128 positions; 7: 112, whose tile count fills the chip's rounds better for some
-// grids). Eight MMA waves, two per SIMD, so that one computes while the other waits for
-// its fragments or the slab barrier (with one per SIMD the matrix pipe was busy ~40% of
-// the time); each takes one position half (blocks 0-3 or 4..FM-1) and one channel
-// quarter. Waves w and w+4 share a SIMD: with FM = 8 wave w takes position half w%2 and
-// quarter w/2; with FM = 7 the two waves of a SIMD take different position halves (4 + 3
-// blocks on every SIMD), and each channel half (the quarters of a half tile) still spans
-// all four SIMDs. The loader waves follow the MMA waves.
-//
-// Slab order: for each kernel row r of the taps and each 64-channel chunk, the three taps
-// (r, 0), (r, 1), (r, 2) in turn (1-2% faster than all channels of one tap in turn).
-template <bool TR, int FM>
+// TR: input gradient (W read transposed); else forward.
+template <bool TR, int WP, int WK>
 __global__ void __launch_bounds__(768, 1) conv_nt_kernel(CvArgs a) {
-  static_assert(FM == 8 || FM == 7, "tile");
-  constexpr int NMW = 8;
-  constexpr int BM = 16 * FM;
-  constexpr int NT = 64 * (NMW + 4);
-  constexpr int FMW = 4;               // position blocks per MMA wave (at most)
+  constexpr int WC = 8 / (WP * WK);
+  constexpr int BN = 64 * WC;
+  constexpr int RA = cv_slab_rows(WP);
   constexpr uint32_t OOB = 0x80000000u;
-  constexpr int ASLOT = BM * 128;
-  constexpr int WRING = CV_NW * CV_WSLOT, ARING = CV_NA * ASLOT;
-  __shared__ __attribute__((aligned(1024))) char smem[WRING + ARING];
-  static_assert(WRING + ARING <= 160 * 1024, "LDS");
-  static_assert(BM * CV_PITCH * 4 <= WRING + ARING, "staging");
+  constexpr int WSLOT = BN * 128, ASLOT = RA * 128;
+  constexpr int WRING = CV_NW * WSLOT, ARING = 2 * ASLOT;
+  constexpr int LDS = WRING + ARING + (WK == 2 ? CV_XBUF : 0);
+  static_assert(WP * WC * WK == 8 && (WK == 1 || WP * WC == 4), "eight waves");
+  static_assert(LDS <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(1024))) char smem[LDS];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // The first gfull workgroups take whole tiles (padded to a multiple of 8; consecutive
-  // tiles, which share shifted activation rows, run on one XCD). The workgroups after
-  // them take the last tiles in 128-channel halves, two per tile, so that the chip's last
-  // round of workgroups is a short one.
-  int b, hc = -1;
-  if ((int)blockIdx.x < a.gfull) {
-    b = (int)((blockIdx.x & 7) * (a.gfull >> 3) + (blockIdx.x >> 3));
-    if (b >= a.tfull) return;
-  } else {
-    const int j = (int)blockIdx.x - a.gfull;
-    b = a.tfull + (j >> 1);
-    hc = j & 1;
-  }
-  if (b >= a.tiles) return;
-  const int m0 = b * BM;
+  // consecutive shares, and the channel tiles of one share, run on one XCD
+  const int G = gridDim.x;
+  const int l = (int)(blockIdx.x & 7) * (G >> 3) + (int)(blockIdx.x >> 3);
+  if (l >= a.groups * a.nct) return;
+  const int gr = l / a.nct, n0 = (l - gr * a.nct) * BN;
+  const int b0 = (int)((int64_t)gr * a.nblk / a.groups);
+  const int nb = (int)((int64_t)(gr + 1) * a.nblk / a.groups) - b0;
+  const int nt = (nb + a.tmax - 1) / a.tmax;
+  auto tile0 = [&](int t) { return b0 + t * nb / nt; };  // first block of tile t (tile nt: the end)
   const int Hp = a.H + 2, Wp = a.W + 2;
-  const int nsl = 9 * a.Ck / CV_KS;
+  const int nch = a.Ck / 64, ntr = 3 * nch, nsl = 3 * ntr;  // chunks; triples and slabs of a tile
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
-  const uint32_t ldsw = lds0, ldsa = lds0 + WRING;
-  // tap (3 r + s) and channel offset of slab S: triple q = S / 3 is kernel row q / nch and
-  // channel chunk q % nch, and S % 3 the tap's column s
-  const int nch = a.Ck / CV_KS;
-  auto tap_of = [&](int S, int *c0) {
-    const int q = S / 3, r = q / nch;
-    *c0 = (q - r * nch) * CV_KS;
-    return 3 * r + (S - 3 * q);
-  };
+  const uint32_t ldsw = lds0, ldsa = lds0 + WRING, ldsx = ldsa + ARING;
 
-  if (wave >= NMW + 2) {
+  if (wave >= 10) {
     // --------------------------------------------------------------- weight loaders
-    const int ww = wave - NMW - 2;  // loads the slab rows of channels 128 ww .. 128 ww + 127
-    const bool on = hc < 0 || ww == hc;
-    const i32x4 rw = buf_rsrc(a.w, (uint32_t)((int64_t)9 * a.Ck * CV_BN * 2));
-    uint32_t base[16];
-    uint32_t dst[16];
+    constexpr int QW = WSLOT / 2048;  // 1 KB blocks per wave
+    const int ww = wave - 10;
+    const i32x4 rw = buf_rsrc(a.w, (uint32_t)a.w_bytes);
+    uint32_t base[QW], dst[QW];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int blk = 16 * ww + q;  // 1 KB block of the slot
+    for (int q = 0; q < QW; ++q) {
+      const int blk = QW * ww + q;
       if constexpr (!TR) {
-        // W row o = 8 blk + lane/8, 16-byte chunk (lane%8) ^ swz
+        // W row n0 + 8 blk + lane/8 (rows past C_out: past the buffer), chunk (lane%8) ^ swz
         const int r = 8 * blk + (lane >> 3);
         const int c = (lane & 7) ^ cv_swz_kc(r);
-        base[q] = (uint32_t)(((int64_t)r * 9 * a.Ck + 8 * c) * 2);
+        base[q] = n0 + r < a.Cn ? (uint32_t)(((int64_t)(n0 + r) * 9 * a.Ck + 8 * c) * 2) : OOB;
         dst[q] = (uint32_t)(blk * 1024);
       } else {
-        // quarter h (input channels 64h..64h+63), k-row (output channel) r of the slab
+        // quarter h (input channels n0 + 64h ..), k-row (output channel) r of the slab
         const int h = blk >> 3, g = blk & 7;
         const int r = 8 * g + (lane >> 3);
         const int c = (lane & 7) ^ cv_swz_tr(r);
-        base[q] = (uint32_t)(((int64_t)r * 9 * a.Cw + 64 * h + 8 * c) * 2);
+        base[q] = n0 + 64 * h < a.Cn ? (uint32_t)(((int64_t)r * 9 * a.Ci + n0 + 64 * h + 8 * c) * 2) : OOB;
         dst[q] = (uint32_t)(h * CV_QSLOT + g * 1024);
       }
     }
-    auto issue = [&](int S) {
-      if (!on) return;  // a half tile's other channels: no loads, the same barriers
-      const uint32_t slot = ldsw + (uint32_t)((S % CV_NW) * CV_WSLOT);
-      uint32_t off = OOB;
-      if (S < nsl) {
-        int c0;
-        const int t = tap_of(S, &c0);
-        if constexpr (!TR) off = (uint32_t)((t * a.Ck + c0) * 2);
-        else off = (uint32_t)(((int64_t)c0 * 9 + t) * a.Cw * 2);
+    // the slab to issue next: tap column s of (kernel row r, chunk ch); its ring slot
+    int s = 0, ch = 0, r = 0, left = nt * nsl;
+    uint32_t slot = ldsw;
+    auto issue = [&]() {
+      const uint32_t off = TR ? (uint32_t)(((int64_t)ch * 64 * 9 + 3 * r + s) * a.Ci * 2)
+                              : (uint32_t)(((3 * r + s) * a.Ck + ch * 64) * 2);
+      // (a channel past the last one: OOB plus any slab's offset stays past the buffer)
+      if (left-- > 0) {
+#pragma unroll
+        for (int q = 0; q < QW; ++q) dma16(rw, base[q] + off, slot + dst[q]);
+      } else {  // no slab left: as many loads, all out of range
+#pragma unroll
+        for (int q = 0; q < QW; ++q) dma16(rw, OOB, slot + dst[q]);
       }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) dma16(rw, off == OOB ? OOB : base[q] + off, slot + dst[q]);
-    };
-#pragma unroll
-    for (int S = 0; S < CV_NW - 1; ++S) issue(S);
-    for (int S = 0; S < nsl; ++S) {
-      vm_barrier<16 * (CV_NW - 2)>();  // slab S landed: B_S
-      issue(S + CV_NW - 1);            // into the slot of S-1
-    }
-    vm_barrier<0>();
-  } else if (wave >= NMW) {
-    // ----------------------------------------------------------- activation loaders
-    // The rows of the tile's BM output positions in the padded grid, shifted by the slab's
-    // tap; positions past the last one read as zero. Wave aw fills the 1 KB blocks
-    // FM*aw .. FM*aw + FM-1 (8 rows each).
-    const int aw = wave - NMW;
-    const i32x4 ra = buf_rsrc(a.act, (uint32_t)((int64_t)a.N * Hp * Wp * a.Ck * 2));
-    uint32_t base[FM];
-#pragma unroll
-    for (int q = 0; q < FM; ++q) {
-      const int r = 8 * (FM * aw + q) + (lane >> 3);
-      const int c = (lane & 7) ^ cv_swz_kc(r);
-      const int p = m0 + r;
-      uint32_t bq = OOB;  // OOB + any slab offset stays past the buffer's end
-      if (p < a.M) {
-        const int n = p / (a.H * a.W), rem = p - n * a.H * a.W, h = rem / a.W, w = rem - h * a.W;
-        bq = (uint32_t)(((int64_t)((n * Hp + h) * Wp + w) * a.Ck + 8 * c) * 2);
-      }
-      base[q] = bq;
-    }
-    const uint32_t d0 = ldsa + (uint32_t)(FM * aw * 1024);
-    auto issue = [&](int S) {
-      const uint32_t slot = d0 + (uint32_t)((S % CV_NA) * ASLOT);
-      uint32_t off = OOB;
-      if (S < nsl) {
-        int c0;
-        const int t = tap_of(S, &c0);
-        const int r = t / 3, s = t - 3 * r;
-        const int shift = TR ? (2 - r) * Wp + 2 - s : r * Wp + s;
-        off = (uint32_t)(((int64_t)shift * a.Ck + c0) * 2);
-      }
-#pragma unroll
-      for (int q = 0; q < FM; ++q) dma16(ra, off == OOB ? OOB : base[q] + off, slot + (uint32_t)(q * 1024));
-    };
-#pragma unroll
-    for (int S = 0; S < CV_NA - 1; ++S) issue(S);
-    for (int S = 0; S < nsl; ++S) {
-      vm_barrier<FM * (CV_NA - 2)>();  // slab S landed: B_S
-      issue(S + CV_NA - 1);           // into the slot of S-1
-    }
-    vm_barrier<0>();
-  } else if (hc >= 0 && (wave >> 2) != hc) {
-    // ------------------------------- MMA waves of a half tile's other channels: the slab
-    // barriers B_0 .. B_nsl only
-    for (int S = 0; S <= nsl; ++S) lds_barrier();
-  } else {
-    // --------------------------------------------------------------- MMA group
-    const int fi = lane & 15, kg = lane >> 4;
-    const int sim = wave & 3, j4 = wave >> 2;
-    const int nq = FM == 8 ? wave >> 1 : 2 * j4 + (sim >> 1);    // channel quarter of the wave
-    const int ph = FM == 8 ? wave & 1 : (sim & 1) ^ j4;          // position half
-    const int mb0 = FMW * ph;                                    // first position block
-    const int nbw = ph == 0 ? FMW : FM - FMW;                    // its position blocks
-    const int nb0 = 4 * nq;                                      // first 16-channel block
-    uint32_t fa[FMW], fx[4];
-#pragma unroll
-    for (int i = 0; i < FMW; ++i) fa[i] = (uint32_t)((16 * (mb0 + i) + fi) * 128);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if constexpr (!TR) {
-        fx[j] = (uint32_t)((16 * (nb0 + j) + fi) * 128);
-      } else {
-        // k-rows 8kg + fi/4 (+4) at channels 16j + 4(fi%4) of quarter nq: the transpose
-        // read hands lane fi the four consecutive k of channel 16j + fi
-        const int r = 8 * kg + (fi >> 2);
-        const int c = (2 * j + ((fi >> 1) & 1)) ^ cv_swz_tr(r);
-        fx[j] = (uint32_t)(nq * CV_QSLOT + r * 128 + c * 16 + 8 * (fi & 1));
-      }
-    }
-    const int sw = cv_swz_kc(fi);
-
-    f32x4 acc[FMW][4];
-#pragma unroll
-    for (int i = 0; i < FMW; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    bf16x8 av[2][FMW], wv[2][4];
-    auto read = [&](uint32_t as, uint32_t ws, int s, bf16x8 (&ad)[FMW], bf16x8 (&wd)[4]) {
-      const uint32_t co = (uint32_t)(((4 * s + kg) ^ sw) * 16);
-#pragma unroll
-      for (int i = 0; i < FMW; ++i)
-        if (i < nbw)
-          ad[i] = __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4 *)(uintptr_t)(as + fa[i] + co));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if constexpr (!TR) {
-          wd[j] = __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4 *)(uintptr_t)(ws + fx[j] + co));
-        } else {
-          lds_i16x4 *p = (lds_i16x4 *)(uintptr_t)(ws + fx[j] + (uint32_t)(s * 4096));
-          const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p);
-          const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p + 4 * 128 / 8);
-          wd[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      slot = slot + WSLOT == ldsw + WRING ? ldsw : slot + WSLOT;
+      if (++s == 3) {
+        s = 0;
+        if (++ch == nch) {
+          ch = 0;
+          r = r == 2 ? 0 : r + 1;
         }
       }
     };
-    auto mma = [&](const bf16x8 (&af)[FMW], const bf16x8 (&wf)[4]) {
 #pragma unroll
-      for (int i = 0; i < FMW; ++i)
-        if (i < nbw)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], wf[j], acc[i][j], 0, 0, 0);
-    };
-
-    uint32_t as = ldsa, ws = ldsw;  // slots of the slab being read
-    lds_barrier();                  // B_0: slab 0 landed
-    read(as, ws, 0, av[0], wv[0]);
-    for (int S = 0; S < nsl; ++S) {
-      read(as, ws, 1, av[1], wv[1]);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(av[0], wv[0]);
-      __builtin_amdgcn_sched_barrier(0);
-      lds_barrier();  // B_{S+1}: every read of slab S has landed; publish S+1, free S
-      as = ldsa + (uint32_t)(((S + 1) % CV_NA) * ASLOT);
-      ws = ldsw + (uint32_t)(((S + 1) % CV_NW) * CV_WSLOT);
-      read(as, ws, 0, av[0], wv[0]);  // past the last slab this reads a spent slot, unused
-      __builtin_amdgcn_sched_barrier(0);
-      mma(av[1], wv[1]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // ---- stage the tile as [position][channel] fp32 (pitch 260 floats: the 64 lanes of
-    // one store hit 64 different banks). All of LDS is free: every wave has passed B_nsl,
-    // and every loader had drained its loads before it.
-    float *stg = reinterpret_cast<float *>(smem);
-#pragma unroll
-    for (int i = 0; i < FMW; ++i)
-      if (i < nbw)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) stg[(16 * (mb0 + i) + 4 * kg + e) * CV_PITCH + 16 * (nb0 + j) + fi] = acc[i][j][e];
-  }
-  lds_barrier();
-  // ---- write the tile's rows (output position p is row p of the output); a half tile
-  // its 128 channels
-  const float *stg = reinterpret_cast<const float *>(smem);
-  if (a.out_bf16) {
-    // 8 channels per thread, 32 (16) threads per row
-    const int ch = hc < 0 ? (tid & 31) : 16 * hc + (tid & 15), sub = hc < 0 ? tid >> 5 : tid >> 4;
-    const int step = hc < 0 ? NT / 32 : NT / 16;
-    for (int m = sub; m < BM; m += step) {
-      const int p = m0 + m;
-      if (p < a.M) {
-        const f32x4 v0 = *reinterpret_cast<const f32x4 *>(stg + m * CV_PITCH + 8 * ch);
-        const f32x4 v1 = *reinterpret_cast<const f32x4 *>(stg + m * CV_PITCH + 8 * ch + 4);
-        u32x4 pk;
-        pk[0] = cvt_pk_bf16(v0[0], v0[1]);
-        pk[1] = cvt_pk_bf16(v0[2], v0[3]);
-        pk[2] = cvt_pk_bf16(v1[0], v1[1]);
-        pk[3] = cvt_pk_bf16(v1[2], v1[3]);
-        uint16_t *o = reinterpret_cast<uint16_t *>(a.out) + (int64_t)p * CV_BN + 8 * ch;
-        *reinterpret_cast<u32x4 *>(o) = pk;
+    for (int S = 0; S < CV_NW - 2; ++S) issue();
+    for (int t = 0; t < nt; ++t) {
+      for (int S = 0; S < nsl; ++S) {
+        vm_barrier<QW * (CV_NW - 3)>();  // slab S landed: B_S
+        issue();                         // into the slot of S-2 (reads of S-1 may be in flight)
+        if (WK == 2 && S == 0 && t > 0) {
+          lds_barrier();  // the exchange of the tile before
+          lds_barrier();
+        }
       }
     }
+    vm_barrier<0>();
+    if (WK == 2) {
+      lds_barrier();
+      lds_barrier();
+    }
+  } else if (wave >= 8) {
+    // ----------------------------------------------------------- activation loaders
+    // LDS row u of a tile's slab is column e % (W+2) of the image row e / (W+2) rows after
+    // the tile's first, e = u + (the first position's column): a piece ends with the two
+    // columns after its last position, and the next row's piece starts at column 0.
+    constexpr int QA = RA / 16;  // 8-row blocks per wave: blocks aw, aw + 2, ...
+    const int aw = wave - 8;
+    const i32x4 ra = buf_rsrc(a.act, (uint32_t)((int64_t)a.N * Hp * Wp * a.Ck * 2));
+    const float invw = 1.0f / (float)Wp, invh = 1.0f / (float)a.H;
+    uint32_t base[QA];
+    int rows = 0;
+    auto set_tile = [&](int t) {
+      const int m0 = tile0(t) * 16, cnt = min(tile0(t + 1) * 16, a.M) - m0;
+      const int hr0 = m0 / a.W, w0 = m0 - hr0 * a.W;
+      const int img0 = hr0 / a.H, h0 = hr0 - img0 * a.H;
+      rows = cnt + 2 * ((w0 + cnt - 1) / a.W) + 2;
+#pragma unroll
+      for (int q = 0; q < QA; ++q) {
+        const int u = 8 * (2 * q + aw) + (lane >> 3);
+        const int c = (lane & 7) ^ cv_swz_kc(u);
+        const int e = u + w0, seg = cv_div(e, invw), col = e - seg * Wp;
+        const int dn = cv_div(h0 + seg, invh), h = h0 + seg - dn * a.H;
+        base[q] = u < rows ? (uint32_t)(((int64_t)(((img0 + dn) * Hp + h) * Wp + col) * a.Ck + 8 * c) * 2) : OOB;
+      }
+    };
+    int ch = 0, r = 0;  // the triple to issue next
+    uint32_t slot = ldsa;
+    auto issue = [&]() {
+      const uint32_t off = (uint32_t)(((int64_t)(TR ? 2 - r : r) * Wp * a.Ck + ch * 64) * 2);
+      int left = rows - 8 * aw;
+      asm volatile("" : "+s"(left));  // keeps the blocks' tests here: hoisted, they take 2 QA scalar registers
+#pragma unroll
+      for (int q = 0; q < QA; ++q)
+        if (16 * q < left) dma16(ra, base[q] + off, slot + (uint32_t)((2 * q + aw) * 1024));
+      slot = slot == ldsa ? ldsa + ASLOT : ldsa;
+      if (++ch == nch) {
+        ch = 0;
+        r = r == 2 ? 0 : r + 1;
+      }
+    };
+    set_tile(0);
+    issue();
+    for (int t = 0; t < nt; ++t) {
+      for (int q = 0; q < ntr; ++q) {
+        vm_barrier<0>();  // triple q landed: B_{3q}
+        // into the slot of the triple before
+        if (q + 1 < ntr) {
+          issue();
+        } else if (t + 1 < nt) {
+          set_tile(t + 1);
+          issue();
+        }
+        if (WK == 2 && q == 0 && t > 0) {
+          lds_barrier();
+          lds_barrier();
+        }
+        lds_barrier();
+        lds_barrier();
+      }
+    }
+    vm_barrier<0>();
+    if (WK == 2) {
+      lds_barrier();
+      lds_barrier();
+    }
   } else {
-    // 4 channels per thread, 64 (32) threads per row
-    const int ch = hc < 0 ? (tid & 63) : 32 * hc + (tid & 31), sub = hc < 0 ? tid >> 6 : tid >> 5;
-    const int step = hc < 0 ? NT / 64 : NT / 32;
-    for (int m = sub; m < BM; m += step) {
-      const int p = m0 + m;
-      if (p < a.M) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(stg + m * CV_PITCH + 4 * ch);
-        float *o = reinterpret_cast<float *>(a.out) + (int64_t)p * CV_BN + 4 * ch;
-        *reinterpret_cast<f32x4 *>(o) = v;
+    // --------------------------------------------------------------- MMA group
+    // The waves w and w + 4 share a SIMD: their position groups differ, so that a tile
+    // whose groups hold unequal numbers of blocks still loads the SIMDs evenly.
+    const int fi = lane & 15, kg = lane >> 4;
+    const int hi = wave >> 2;
+    const int kh = WK == 2 ? hi : 0;
+    const int c = WP == 4 ? (WK == 2 ? 0 : hi) : (wave >> 1) & 1;
+    const int p = WP == 4 ? (wave + 2 * hi) & 3 : (wave ^ hi) & 1;
+    const bool live = n0 + 64 * c < a.Cn;
+    const float invw = 1.0f / (float)a.W;
+    uint32_t fx;  // weight fragment of block 0, k-step kh
+    if constexpr (!TR) {
+      fx = (uint32_t)((64 * c + fi) * 128 + (((4 * kh + kg) ^ cv_swz_kc(fi)) * 16));
+    } else {
+      // k-rows 8kg + fi/4 (+4) at channels 16j + 4(fi%4) of quarter c: the transpose
+      // read hands lane fi the four consecutive k of channel 16j + fi (block j: chunk ^ 2j)
+      const int r = 8 * kg + (fi >> 2);
+      fx = (uint32_t)(c * CV_QSLOT + (32 * kh + r) * 128 + ((((fi >> 1) & 1) ^ cv_swz_tr(r)) * 16) + 8 * (fi & 1));
+    }
+    uint32_t ws = ldsw, as = ldsa;  // slots of the slab being read
+    auto next_w = [&]() { ws = ws + WSLOT == ldsw + WRING ? ldsw : ws + WSLOT; };
+    lds_barrier();  // B_0: slab 0 landed
+
+    auto tile = [&](auto nbtag, int t, int first) {
+      constexpr int NB = decltype(nbtag)::value;  // position blocks of the wave, from block `first`
+      const int m0 = tile0(t) * 16, w0 = m0 % a.W;
+      uint32_t adr[3][NB];  // activation fragments of k-step kh (tap column, block)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int pos = 16 * (first + i) + fi;
+        const int u = pos + 2 * cv_div(w0 + pos, invw);
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          const int row = u + (TR ? 2 - s : s);
+          adr[s][i] = (uint32_t)(row * 128 + (((4 * kh + kg) ^ cv_swz_kc(row)) * 16));
+        }
+      }
+      f32x4 acc[NB][4];
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      // Fragments: the activations' in place (block i is read anew as soon as its MFMAs have
+      // been issued), the weights' in two sets.
+      bf16x8 av[NB], wv[2][4];
+      auto read_a = [&](int s, int k, int i) {
+        const uint32_t kx = (uint32_t)(64 * k);  // four chunks on
+        av[i] = __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4 *)(uintptr_t)(as + (adr[s][i] ^ kx)));
+      };
+      auto read_w = [&](int k, bf16x8 (&wd)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (!TR) {
+            wd[j] = __builtin_bit_cast(bf16x8, *(const __attribute__((address_space(3))) u32x4 *)(uintptr_t)(ws + (fx ^ (uint32_t)(64 * k)) + (uint32_t)(2048 * j)));
+          } else {
+            lds_i16x4 *q = (lds_i16x4 *)(uintptr_t)(ws + (fx ^ (uint32_t)(32 * j)) + (uint32_t)(k * 4096));
+            const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(q);
+            const i16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(q + 4 * 128 / 8);
+            wd[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+          }
+        }
+      };
+      // One k-step: the MFMAs of the fragments at hand (weight set `cur`), and between them
+      // the reads of the next k-step (tap column s, step k of the slab at ws / as).
+      auto step = [&](auto curtag, int s, int k) {
+        constexpr int cur = decltype(curtag)::value;
+        read_w(k, wv[cur ^ 1]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[cur][j], av[i], acc[i][j], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          read_a(s, k, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      // The barrier between two slabs, B_{S+1}. A weight slot is written anew two slabs after
+      // its last reads were issued (every one of them has been waited for by then), an
+      // activation slot right after the barrier that ends its triple, which waits for them.
+      auto slab_end = [&](int s) {
+        if (s == 2) {
+          lds_barrier();
+          as = as == ldsa ? ldsa + ASLOT : ldsa;
+        } else {
+          asm volatile("s_barrier" : : : "memory");
+        }
+        next_w();
+      };
+#pragma unroll
+      for (int i = 0; i < NB; ++i) read_a(0, 0, i);
+      read_w(0, wv[0]);
+      // (past a tile's last slab the next tile's slab is read at this tile's rows, unused)
+      if constexpr (WK == 1) {
+        for (int q = 0; q < ntr; ++q) {
+#pragma unroll
+          for (int s = 0; s < 3; ++s) {
+            step(CvInt<0>{}, s, 1);
+            slab_end(s);
+            step(CvInt<1>{}, (s + 1) % 3, 0);
+          }
+        }
+      } else {
+        // the wave's k-step of each slab
+        auto triple = [&](auto partag) {
+          constexpr int par = decltype(partag)::value;
+#pragma unroll
+          for (int s = 0; s < 3; ++s) {
+            slab_end(s);
+            if ((par + s) & 1) step(CvInt<1>{}, (s + 1) % 3, 0);
+            else step(CvInt<0>{}, (s + 1) % 3, 0);
+          }
+        };
+        for (int q = 0;;) {
+          triple(CvInt<0>{});
+          if (++q == ntr) break;
+          triple(CvInt<1>{});
+          if (++q == ntr) break;
+        }
+        // the halves' sums: the second half's wave hands over its first two blocks and takes
+        // the first's last two
+        const uint32_t xs = ldsx + (uint32_t)((c * WP + p) * 8192 + lane * 16);
+        auto xat = [&](int i, int j) {
+          return (__attribute__((address_space(3))) f32x4 *)(uintptr_t)(xs + (uint32_t)(((i & 1) * 4 + j) * 1024));
+        };
+        auto give = [&](int i0) {
+#pragma unroll
+          for (int i = i0; i < i0 + 2; ++i)
+            if (i < NB)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) *xat(i, j) = acc[i < NB ? i : 0][j];
+        };
+        auto take = [&](int i0) {
+#pragma unroll
+          for (int i = i0; i < i0 + 2; ++i)
+            if (i < NB)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) acc[i < NB ? i : 0][j] += *xat(i, j);
+        };
+        if (kh == 1) give(0);
+        lds_barrier();
+        if (kh == 0) {
+          take(0);
+          give(2);
+        }
+        lds_barrier();
+        if (kh == 1) take(2);
+      }
+      // ---- write the tile: lane (fi, kg) holds channels 16j + 4kg .. +3 of position fi of
+      // each block; bf16: blocks 2t and 2t+1 exchanged between the lanes so that each
+      // holds eight channels
+      const int nc0 = n0 + 64 * c;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (WK == 2 && (i >> 1) != kh) continue;
+        const int pos = m0 + 16 * (first + i) + fi;
+        if (a.out_bf16) {
+          uint16_t *o = reinterpret_cast<uint16_t *>(a.out) + (int64_t)pos * a.Cn + nc0 + 16 * (kg & 1) + 8 * (kg >> 1);
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const f32x4 x = acc[i][2 * b], y = acc[i][2 * b + 1];
+            const auto lo = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(y[0], y[1]), false, false);
+            const auto up = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(x[2], x[3]), cvt_pk_bf16(y[2], y[3]), false, false);
+            if (pos < a.M) *reinterpret_cast<u32x4 *>(o + 32 * b) = u32x4{lo[0], up[0], lo[1], up[1]};
+          }
+        } else if (pos < a.M) {
+          float *o = reinterpret_cast<float *>(a.out) + (int64_t)pos * a.Cn + nc0 + 4 * kg;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) *reinterpret_cast<f32x4 *>(o + 16 * j) = acc[i][j];
+        }
+      }
+    };
+
+    for (int t = 0; t < nt; ++t) {
+      // the tile's blocks over the position groups, as evenly as they go
+      const int n = tile0(t + 1) - tile0(t);
+      const int mine = live ? n / WP + (p < n % WP ? 1 : 0) : 0, first = p * (n / WP) + min(p, n % WP);
+      switch (mine) {
+        case 4: tile(CvInt<4>{}, t, first); break;
+        case 3: tile(CvInt<3>{}, t, first); break;
+        case 2: tile(CvInt<2>{}, t, first); break;
+        case 1: tile(CvInt<1>{}, t, first); break;
+        default:  // no block here: the slab barriers (and the exchange's)
+          for (int S = 0; S < nsl + (WK == 2 ? 2 : 0); ++S) lds_barrier();
+          // the ring positions after the tile
+          for (int S = 0; S < nsl % CV_NW; ++S) next_w();
+          if (ntr & 1) as = as == ldsa ? ldsa + ASLOT : ldsa;
       }
     }
   }
@@ -583,9 +701,11 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
   if (opt(IMBD_OPT_CONV_NT) == 0) return false;  // the tiled GEMM template instead
   const int Cn = pass == 1 ? Co : Ci, Ck = pass == 1 ? Ci : Co;
   auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
-  const int64_t rows = (int64_t)N * (H + 2) * (W + 2) + 2 * (W + 2) + 2 + CV_BM;
-  return (pass == 1 || pass == 2) && N >= 1 && H >= 1 && W >= 1 && Cn == CV_BN && Ck >= 64 && Ck % 64 == 0 &&
-         al(act) && al(w) && al(out) && rows * Ck * 2 < ((int64_t)1 << 31) &&
+  // byte offsets of both operands within one buffer descriptor; image rows and columns
+  // within the range of the kernel's short divisions
+  return (pass == 1 || pass == 2) && N >= 1 && H >= 1 && W >= 1 && Cn >= 64 && Cn % 64 == 0 && Ck >= 64 &&
+         Ck % 64 == 0 && al(act) && al(w) && al(out) && H < 32768 && W < 32768 &&
+         (int64_t)N * (H + 2) * (W + 2) * Ck * 2 < ((int64_t)1 << 31) &&
          (int64_t)9 * Ci * Co * 2 < ((int64_t)1 << 31);
 }
 
@@ -643,41 +763,31 @@ int run_conv_nt(int pass, int N, int H, int W, int Ci, int Co, const void *act, 
   a.H = H;
   a.W = W;
   a.Ck = pass == 1 ? Ci : Co;
-  a.Cw = Ci;
+  a.Cn = pass == 1 ? Co : Ci;
+  a.Ci = Ci;
+  a.w_bytes = (int64_t)9 * Ci * Co * 2;
   a.M = N * H * W;
-  // One workgroup per CU (160 KB of LDS): past one round, the tiles of a short last round
-  // run as 128-channel halves on twice as many CUs, which ends that round sooner. The tile
-  // height (128 or 112 positions) is the one whose rounds (a round of halves counted as
-  // half a round) take fewer position blocks per CU: on the 32 x 56 x 56 grid, 784 tiles
-  // of 128 (3 rounds and a short one) against 896 of 112 (3 rounds and a full round of
-  // halves).
-  auto plan = [&](int fm, int *tiles, int *last, bool *halves) {
-    *tiles = (a.M + 16 * fm - 1) / (16 * fm);
-    *last = *tiles > CV_CUS ? *tiles % CV_CUS : 0;
-    *halves = *last > 0 && 2 * *last <= CV_CUS;
-    const int rounds = (*tiles + CV_CUS - 1) / CV_CUS;
-    return (*halves ? 2 * rounds - 1 : 2 * rounds) * fm;  // in half rounds x blocks
-  };
-  int t8, l8, t7, l7;
-  bool h8, h7;
-  const int c8 = plan(8, &t8, &l8, &h8), c7 = plan(7, &t7, &l7, &h7);
+  a.nblk = (a.M + 15) / 16;
+  const bool narrow = a.Cn == 64;
+  a.nct = narrow ? 1 : (a.Cn + 127) / 128;
+  // one workgroup per CU (the LDS of each), every one with a share of the position blocks
+  a.groups = std::max(1, std::min(a.nblk, CV_CUS / a.nct));
+  const int share = (a.nblk + a.groups - 1) / a.groups;
   const int o = opt(IMBD_OPT_CONV_NT);
-  const int fm = o == 2 ? 8 : o == 3 ? 7 : (c7 < c8 ? 7 : 8);
-  a.tiles = fm == 8 ? t8 : t7;
-  const int last = fm == 8 ? l8 : l7;
-  const bool halves = fm == 8 ? h8 : h7;
-  a.tfull = halves ? a.tiles - last : a.tiles;
-  a.gfull = (a.tfull + 7) / 8 * 8;
-  const int grid = a.gfull + (halves ? 2 * last : 0);
+  const bool tall = narrow || share > 8 || o >= 2;
+  // blocks per tile: what the MMA waves hold and what the activation slab's rows allow (a
+  // tile of n positions touches at most (W - 1 + n - 1) / W + 1 image rows)
+  const int cap = cv_slab_rows(tall ? 4 : 2);
+  a.tmax = tall ? 16 : 8;
+  if (o >= 2) a.tmax = o == 2 ? 8 : 7;
+  while (a.tmax > 1 && 16 * a.tmax + 2 * ((W + 16 * a.tmax - 2) / W) + 2 > cap) --a.tmax;
+  const int grid = (a.groups * a.nct + 7) / 8 * 8;
   {
     LaunchTimer t(pass == 1 ? IMBD_K_CONV_FWD : IMBD_K_CONV_DGRAD, 0, s);
-    if (pass == 1) {
-      if (fm == 8) hipLaunchKernelGGL((conv_nt_kernel<false, 8>), dim3(grid), dim3(768), 0, s, a);
-      else hipLaunchKernelGGL((conv_nt_kernel<false, 7>), dim3(grid), dim3(768), 0, s, a);
-    } else {
-      if (fm == 8) hipLaunchKernelGGL((conv_nt_kernel<true, 8>), dim3(grid), dim3(768), 0, s, a);
-      else hipLaunchKernelGGL((conv_nt_kernel<true, 7>), dim3(grid), dim3(768), 0, s, a);
-    }
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(768), 0, s, a); };
+    if (narrow) pass == 1 ? go(conv_nt_kernel<false, 4, 2>) : go(conv_nt_kernel<true, 4, 2>);
+    else if (tall) pass == 1 ? go(conv_nt_kernel<false, 4, 1>) : go(conv_nt_kernel<true, 4, 1>);
+    else pass == 1 ? go(conv_nt_kernel<false, 2, 2>) : go(conv_nt_kernel<true, 2, 2>);
   }
   return check_launch("conv_nt");
 }

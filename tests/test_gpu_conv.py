@@ -263,3 +263,33 @@ def test_conv_errors(imbd, dev):
         imbd.conv3x3_tile_wgrad(xd, dyd, dw, ws=torch.zeros(64, dtype=torch.uint8, device=dev))
     assert e.value.status == imbd.IMBD_EWORKSPACE
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("N,H,W,Ci,Co", [
+    # one column wide (three slab rows per position), two; channel tiles half empty (192, 320)
+    (2, 40, 1, 64, 192), (3, 70, 2, 192, 64), (1, 3, 5, 320, 192),
+    # image rows longer than a tile, and a last tile of one position
+    (1, 3, 337, 128, 320), (1, 1, 513, 64, 128),
+    # shares of 9 to 16 blocks (uneven position groups), and of more than 16: two tiles each;
+    # 64 output channels with several tiles (odd number of slab triples)
+    (9, 64, 61, 64, 128), (11, 83, 91, 64, 128), (6, 110, 113, 128, 64), (5, 120, 118, 64, 64),
+    # many output channels of few positions: the two k halves with idle position groups
+    (1, 5, 7, 512, 448), (7, 13, 13, 192, 384)])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_conv_tile_every_channel_count_sampled(imbd, dev, N, H, W, Ci, Co, out_bf16):
+    """Forward and input gradient for channel counts that are multiples of 64:
+    the layouts of the MMA waves, tile heights and slab pieces that the sizes above name. All
+    channels of the first, a middle and the last position and random outputs elsewhere."""
+    import torch
+    _flush(f"conv channels {(N, H, W, Ci, Co)} bf16={out_bf16}")
+    d = make_conv_inputs(N, H, W, Ci, Co, seed=N * 1000 + W, border=(True, False, False, True))
+    xv, wv, dyv = bf16_values(d["x_bits"]), bf16_values(d["w_bits"]), bf16_values(d["dy_bits"])
+    y, dx, _ = _run(imbd, dev, d, out_bf16=out_bf16)
+    rng = np.random.default_rng(W)
+    M = N * H * W
+    rows = np.unique([0, min(16, M - 1), M // 2, M - 1])
+    tol = 2.0 ** -8 + 1e-5 if out_bf16 else 1e-5
+    for got, at, C, a in ((y, oracle.conv3x3_fwd_at, Co, xv), (dx, oracle.conv3x3_dgrad_at, Ci, dyv)):
+        idx = np.concatenate([(rows[:, None] * C + np.arange(C)[None, :]).reshape(-1), rng.integers(0, M * C, 300)])
+        assert nrm_err(host(got).reshape(-1)[idx], at(a, wv, idx)) < tol
+        assert torch.isfinite(got).all().item()
