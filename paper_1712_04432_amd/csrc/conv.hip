@@ -452,247 +452,400 @@ __global__ void __launch_bounds__(768, 1) conv_nt_kernel(CvArgs a) {
 // positions p = (n, h, w), P(p) = (n (H+2) + h) (W+2) + w (Sec. 2.2: the tile's partial of
 // the weight gradient, which the all-reduce over the domain completes). Both operands are
 // position-major, so K = positions and both fragments come from k-row-major LDS slabs
-// through the transpose read. A workgroup owns 256 output channels x 128 input channels
-// of one tap over one range of output positions; the ranges are K splits whose fp32
-// partials the split-K reduce adds in split order. Slabs of 64 positions, each row's
-// padded-grid row P(p) kept incrementally by the loader lane that fetches it:
-//  * waves 6-7 load the Delta_Y slab (64 positions x 256 channels, four 64-channel
-//    quarters);
-//  * waves 4-5 load the shifted activation slab (64 positions x 128 channels);
-//  * waves 0-3 each accumulate 128 output channels x 64 input channels.
-// Rows past the split's range read as zero (their loads are out of range).
+// through the transpose read.
+//
+// A workgroup owns OB = 64 WO output channels x 64 input channels x the three taps of one
+// kernel row over one range of positions. The three taps share both slabs: the Delta_Y slab
+// (64 positions x OB channels) and the activation slab (per image row piece of the slab its
+// positions and the two columns after them, 64 channels), of which a tap reads the rows
+// from its column on: 27 KB into LDS per 48 x 16 MFMAs, where one tap of 128 input
+// channels with slabs of its own took 32 KB per 32 x 16. The ranges are K splits, whose
+// fp32 partials a flat reduce adds in split order (one range writes dW itself).
+//
+// Eight MMA waves, each 64 output channels x 32 input channels x 3 taps:
+//   WO = 2, WK = 2: 128 output channels, the two 32-position steps of each slab to two
+//     halves of the waves, whose sums are added through LDS at the end (five slabs of ring);
+//   WO = 4, WK = 1: 256 output channels, every wave both steps (three slabs).
+// What bounds it is the issue of the MMA waves' other instructions, which the two waves of
+// a SIMD, in step through the slab barriers, do not hide from each other. Left to them are
+// the fragment reads and ten instructions per slab for the fragments' rows; four loader
+// waves do the rest. At 32 x 56 x 56, 256 -> 256 (kernel and reduce): every wave issuing an
+// eighth of the loads and working out swizzled rows per tap 148 us, the rows linear (160
+// bytes apart instead of swizzled, a tap then is an offset) 123, the loads on waves of
+// their own and both operands' fragments read anew in place 110 (with a second Delta_Y
+// set the registers spilled: 170), the reduce with four loads instead of eight in flight
+// on a sixth of the registers 104; the one-tap kernel before 118. Measured (us, before ->
+// after; other channel counts than 256 were on the tiled GEMM template):
+//   64 x 13 x 13, 384 -> 384: 137 -> 40.5      32 x 14 x 14, 512 -> 512: 179 -> 41.7
+//   32 x 56 x 56,  64 -> 128: 200 -> 26.9      16 x 56 x 56, 192 -> 320: 685 -> 62.4
+// Rows past the range read as zero in Delta_Y, and the positions there read a zero row of
+// the activation slab, so no infinity of a neighbouring row reaches a sum.
 struct CwArgs {
   const uint16_t *x;    // x_pad [N][H+2][W+2][Ci]
-  const uint16_t *dy;   // interior start of dy_pad: dy_pad + ((W+2) + 1) * Co
-  float *partial;       // [split][Co][ldp]: element (tap*Ci + c, o) at o*ldp + tap*Ci + c
-  int64_t ldp, sstride;
+  const uint16_t *dy;   // dy_pad [N][H+2][W+2][Co]
+  float *out;           // [split][Co][3][3][Ci], or dW when there is one split
+  int64_t sstride;      // floats from one split to the next
+  uint32_t x_bytes, dy_bytes, out_bytes;
   int H, W, Ci, Co;
-  int M, k_split, splits, tiles;  // output positions N*H*W; tiles = 9 * Ci / 128
-  int Mp;                         // padded-grid rows up to the last output position's
+  int M, k_split, splits, tiles;  // output positions N*H*W; tiles of one split
+  int tco;                        // output-channel tiles
+  int xblk;                       // 1 KB blocks of an activation slab in use
+  int dh, dw;                     // 64 / W, 64 % W: 64 positions on
 };
 
-constexpr int CW_XSLOT = 64 * 256;   // 16 KB: 64 positions x 128 channels
-constexpr int CW_DSLOT = 64 * 512;   // 32 KB: 64 positions x 256 channels
-constexpr int CW_NX = 4, CW_ND = 3;  // ring slots
-constexpr int CW_PITCH = 128 + 4;    // staging row pitch in floats
+// An activation slab: up to 98 rows of 64 channels and three zero rows, 160 bytes apart (ten
+// 16-byte chunks, the last two unused): a transpose read of 16 consecutive rows x 16 channels
+// touches every bank twice whatever row it starts at, and a tap is an offset of 160 bytes.
+constexpr int CW_XPITCH = 160;
+constexpr int CW_XROWS = 98;
+constexpr int CW_XSLOT = 16 * 1024;
+static_assert((CW_XROWS + 3) * CW_XPITCH <= CW_XSLOT, "activation slab");
 
-// Output position p as (h, w) and its padded-grid row P(p); the step to position p + 64
-// without a division (the rows that wrap past an image row or an image are counted).
-__device__ __forceinline__ void cw_row_init(const CwArgs &a, int p, int *h, int *w, int *P) {
-  const int HW = a.H * a.W, n = p / HW, rem = p - n * HW;
-  *h = rem / a.W;
-  *w = rem - *h * a.W;
-  *P = (n * (a.H + 2) + *h) * (a.W + 2) + *w;
-}
-__device__ __forceinline__ void cw_row_next(const CwArgs &a, int *h, int *w, int *P) {
-  const int Wp = a.W + 2, dh = 64 / a.W, dw = 64 - dh * a.W;
-  *w += dw;
-  *h += dh;
-  *P += dh * Wp + dw;
-  if (*w >= a.W) {
-    *w -= a.W;
-    ++*h;
-    *P += 2;
-  }
-  while (*h >= a.H) {
-    *h -= a.H;
-    *P += 2 * Wp;
-  }
-}
+constexpr int cw_slab_rows(int w) { return 64 + 2 * ((w + 62) / w) + 2; }
 
-__global__ void __launch_bounds__(512, 1) conv_wg_kernel(CwArgs a) {
+// 16-byte chunk swizzle of a Delta_Y row (128 bytes apart), to the same end.
+__device__ __forceinline__ int cw_swz(int r) { return ((r >> 1) & 3) << 1; }
+
+template <int WO, int WK>
+__global__ void __launch_bounds__(768, 1) conv_wg_kernel(CwArgs a) {
+  static_assert((WO == 2 && WK == 2) || (WO == 4 && WK == 1), "eight waves, two per 64-channel half");
   constexpr uint32_t OOB = 0x80000000u;
-  constexpr int DRING = CW_ND * CW_DSLOT, XRING = CW_NX * CW_XSLOT;
-  __shared__ __attribute__((aligned(1024))) char smem[DRING + XRING];
-  static_assert(DRING + XRING <= 160 * 1024, "LDS");
-  static_assert(256 * CW_PITCH * 4 <= DRING + XRING, "staging");
+  constexpr int DSLOT = WO * CV_QSLOT, SLOT = DSLOT + CW_XSLOT;
+  constexpr int NS = WK == 2 ? 5 : 3;
+  // slabs issued ahead of the one being read: a slot is written anew two slabs after its last
+  // reads were issued (they need not have landed at the barrier in between), or, with three
+  // slots, after a barrier that waits for them
+  constexpr int AHEAD = WK == 2 ? NS - 2 : NS - 1;
+  __shared__ __attribute__((aligned(1024))) char smem[NS * SLOT];
+  static_assert(NS * SLOT <= 160 * 1024, "LDS");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // padded to a multiple of 8: the tiles of one split (which read the same positions) run
-  // on one XCD
+  // the tiles of one split (which read the same positions) run on one XCD
   const int G = gridDim.x;
-  const int b = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
-  if (b >= a.tiles * a.splits) return;
-  const int split = b / a.tiles, tile = b - split * a.tiles;
-  const int tap = tile / (a.Ci / 128), c0 = (tile - tap * (a.Ci / 128)) * 128;
-  const int klo = split * a.k_split, krange = min(a.M, klo + a.k_split) - klo;
-  const int nsl = krange > 0 ? (krange + 63) / 64 : 0;
-  const int Wp = a.W + 2;
+  const int l = (int)(blockIdx.x & 7) * (G >> 3) + (int)(blockIdx.x >> 3);
+  if (l >= a.tiles * a.splits) return;
+  const int split = l / a.tiles;
+  int tile = l - split * a.tiles;
+  const int o0 = (tile % a.tco) * 64 * WO;
+  tile /= a.tco;
+  const int r3 = tile % 3, c0 = (tile / 3) * 64;
+  const int klo = split * a.k_split, kend = min(a.M, klo + a.k_split);
+  const int nsl = (kend - klo + 63) / 64;
+  const int Hp = a.H + 2, Wp = a.W + 2;
+  const float invw = 1.0f / (float)a.W;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
-  const uint32_t ldsd = lds0, ldsx = lds0 + DRING;
+  auto up = [&](uint32_t slot) { return slot + SLOT == lds0 + NS * SLOT ? lds0 : slot + SLOT; };
 
-  if (wave >= 6) {
-    // ---------------------------------------------------- Delta_Y loaders (6, 7)
-    // blocks 16dw..16dw+15 of a slot: quarter h = blk/8, k-rows 8(blk%8)..+7
-    const int dw = wave - 6;
-    const i32x4 rd = buf_rsrc(a.dy, (uint32_t)((int64_t)a.Mp * a.Co * 2));
-    // the wave's blocks cover quarters 2dw, 2dw+1 of the same 8 row groups g (k-rows
-    // 8g + lane/8)
-    uint32_t col[2][8];
-    int hh[8], ww[8], pp[8];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const int r = 8 * g + (lane >> 3);
-      const int c = (lane & 7) ^ cv_swz_tr(r);
-      col[0][g] = (uint32_t)((64 * (2 * dw) + 8 * c) * 2);
-      col[1][g] = (uint32_t)((64 * (2 * dw + 1) + 8 * c) * 2);
-      cw_row_init(a, klo + r, &hh[g], &ww[g], &pp[g]);
+  // the zero rows of each activation slot
+  for (int i = tid; i < NS * 32; i += 768)
+    if ((i & 31) < 30)
+      *reinterpret_cast<u32x4 *>(smem + (i >> 5) * SLOT + DSLOT + CW_XROWS * CW_XPITCH + (i & 31) * 16) = u32x4{0u, 0u, 0u, 0u};
+  lds_barrier();
+
+  if (wave >= 8) {
+    // ---- loaders: Delta_Y (waves 8, 9) and activations (10, 11). The rows of an activation
+    // slab are one run of the padded grid (two halo rows more at each image's end), so within
+    // an image their offsets are a lane constant plus a scalar; Delta_Y's skip two columns
+    // per image row.
+    const float invwp = 1.0f / (float)Wp, invh = 1.0f / (float)a.H;
+    const int w2 = wave & 1;
+    // the slab to issue: its first position q0 = (row h0 of its image, column w0), row P0 of
+    // the padded grid
+    int q0 = klo, h0, w0, P0;
+    {
+      const int hr = klo / a.W, n = hr / a.H;
+      w0 = klo - hr * a.W;
+      h0 = hr - n * a.H;
+      P0 = (n * Hp + h0) * Wp + w0;
     }
-    auto issue = [&](int S) {
-      const uint32_t slot = ldsd + (uint32_t)((S % CW_ND) * CW_DSLOT);
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {
-        const int r = 8 * g + (lane >> 3);
-        const bool ok = S < nsl && S * 64 + r < krange;
-        const uint32_t off = (uint32_t)pp[g] * (uint32_t)(a.Co * 2);
-#pragma unroll
-        for (int hq = 0; hq < 2; ++hq)
-          dma16(rd, ok ? off + col[hq][g] : OOB, slot + (uint32_t)((2 * dw + hq) * CV_QSLOT + g * 1024));
-        cw_row_next(a, &hh[g], &ww[g], &pp[g]);
+    uint32_t slot = lds0;
+    auto crosses = [&]() {  // whether the 64 positions reach another image: row h0 + (w0 + 63) / W
+      const int t63 = w0 + a.dw - 1;
+      return h0 + a.dh + (t63 >= a.W ? 1 : 0) - (t63 < 0 ? 1 : 0) >= a.H;
+    };
+    auto next = [&]() {
+      slot = up(slot);
+      q0 += 64;
+      w0 += a.dw;
+      h0 += a.dh;
+      P0 += a.dw + a.dh * Wp;
+      if (w0 >= a.W) {
+        w0 -= a.W;
+        ++h0;
+        P0 += 2;
+      }
+      while (h0 >= a.H) {
+        h0 -= a.H;
+        P0 += 2 * Wp;
       }
     };
+    auto run = [&](auto ntag, auto issue) {  // N loads a slab
+      constexpr int N = decltype(ntag)::value;
 #pragma unroll
-    for (int S = 0; S < CW_ND - 1; ++S) issue(S);
-    for (int S = 0; S < nsl; ++S) {
-      vm_barrier<16 * (CW_ND - 2)>();  // slab S landed: B_S
-      issue(S + CW_ND - 1);            // into the slot of S-1
-    }
-    vm_barrier<0>();
-  } else if (wave >= 4) {
-    // --------------------------------------------------- activation loaders (4, 5)
-    // quarter h = blk/8 (channels c0 + 64h ..), k-rows 8(blk%8).. of positions shifted by tap
-    const int xw = wave - 4;
-    const int r3 = tap / 3, s3 = tap - 3 * r3, shift = r3 * Wp + s3;
-    const i32x4 rx = buf_rsrc(a.x, (uint32_t)((int64_t)(a.Mp + 2 * Wp + 2) * a.Ci * 2));
-    // block q of the wave's quarter: k-rows 8q + lane/8
-    uint32_t col[8];
-    int hh[8], ww[8], pp[8];
+      for (int S = 0; S < AHEAD; ++S) issue(ntag);
+      for (int S = 0; S <= nsl; ++S) {
+        vm_barrier<N * (AHEAD - 1)>();  // slab S landed: B_S
+        issue(ntag);
+      }
+    };
+    if (wave < 10) {
+      // row groups 4 w2 .. 4 w2 + 3 (8 positions each) of every 64-channel quarter
+      const i32x4 rd = buf_rsrc(a.dy, a.dy_bytes);
+      const uint32_t d2 = (uint32_t)(a.Co * 2);
+      uint32_t base[4];
+      float rowf[4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r = 8 * q + (lane >> 3);
-      const int c = (lane & 7) ^ cv_swz_tr(r);
-      col[q] = (uint32_t)((c0 + 64 * xw + 8 * c) * 2);
-      cw_row_init(a, klo + r, &hh[q], &ww[q], &pp[q]);
-    }
-    auto issue = [&](int S) {
-      const uint32_t slot = ldsx + (uint32_t)((S % CW_NX) * CW_XSLOT) + (uint32_t)(xw * CV_QSLOT);
+      for (int g = 0; g < 4; ++g) {
+        const int r = 32 * w2 + 8 * g + (lane >> 3);
+        base[g] = (uint32_t)(r + Wp + 1) * d2 + (uint32_t)((o0 + 8 * ((lane & 7) ^ cw_swz(r))) * 2);
+        rowf[g] = (float)r + 0.5f;
+      }
+      run(CvInt<4 * WO>{}, [&](auto) {
+        const uint32_t dP = (uint32_t)P0 * d2;
+        const bool far = crosses(), last = q0 + 64 > kend;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int seg = (int)((rowf[g] + (float)w0) * invw);
+          uint32_t off = base[g] + dP + (uint32_t)__umul24((uint32_t)seg, 2 * d2);
+          if (far) off += (uint32_t)cv_div(h0 + seg, invh) * (uint32_t)(2 * Wp) * d2;
+          if (last && 32 * w2 + 8 * g + (lane >> 3) >= kend - q0) off = OOB;
+#pragma unroll
+          for (int q = 0; q < WO; ++q)
+            dma16(rd, o0 + 64 * q < a.Co ? off + (uint32_t)(128 * q) : OOB,
+                  slot + (uint32_t)(q * CV_QSLOT + (4 * w2 + g) * 1024));
+        }
+        next();
+      });
+    } else {
+      // 1 KB blocks w2, w2 + 2, .. of the slab: chunk L = 64 (w2 + 2q) + lane is chunk L % 10
+      // (the last two unused) of row L / 10
+      const i32x4 rx = buf_rsrc(a.x, a.x_bytes);
+      const uint32_t x2 = (uint32_t)(a.Ci * 2);
+      auto row = [&](int q) { return (64 * (w2 + 2 * q) + lane) / 10; };
+      uint32_t base[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const int r = 8 * q + (lane >> 3);
-        const bool ok = S < nsl && S * 64 + r < krange;
-        const uint32_t off = (uint32_t)(pp[q] + shift) * (uint32_t)(a.Ci * 2);
-        dma16(rx, ok ? off + col[q] : OOB, slot + (uint32_t)(q * 1024));
-        cw_row_next(a, &hh[q], &ww[q], &pp[q]);
+        const int c = 64 * (w2 + 2 * q) + lane - 10 * row(q);
+        // (OOB plus any row's offset stays past the buffer)
+        base[q] = c < 8 && row(q) < CW_XROWS ? (uint32_t)(row(q) + r3 * Wp) * x2 + (uint32_t)((c0 + 8 * c) * 2) : OOB;
       }
-    };
+      auto issue = [&](auto ntag) {
+        constexpr int N = decltype(ntag)::value;
+        const uint32_t xP = (uint32_t)P0 * x2;
+        if (!crosses() && q0 + 64 <= kend) {
 #pragma unroll
-    for (int S = 0; S < CW_NX - 1; ++S) issue(S);
-    for (int S = 0; S < nsl; ++S) {
-      vm_barrier<8 * (CW_NX - 2)>();  // slab S landed: B_S
-      issue(S + CW_NX - 1);           // into the slot of S-1
-    }
-    vm_barrier<0>();
-  } else {
-    // --------------------------------------------------------------- MMA group
-    // wave (wm, wn): output channels 128wm.. (Delta_Y quarters 2wm, 2wm+1), input channels
-    // 64wn.. (activation quarter wn)
-    constexpr int FM = 8;
-    const int fi = lane & 15, kg = lane >> 4;
-    const int wm = wave & 1, wn = wave >> 1;
-    const int r = 8 * kg + (fi >> 2);
-    uint32_t fa[FM], fx[4];
+          for (int q = 0; q < N; ++q) dma16(rx, base[q] + xP, slot + (uint32_t)(DSLOT + (w2 + 2 * q) * 1024));
+        } else {
+          // the slab goes on in the next image (or past several), or is the range's last one
+          // (or past it): rows behind its last position's read as zero
+          const int cnt = min(64, kend - q0), rows = cnt > 0 ? cnt + 2 * ((w0 + cnt - 1) / a.W) + 2 : 0;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int mb = 8 * wm + i, h = mb >> 2, ib = mb & 3;
-      const int c = (2 * ib + ((fi >> 1) & 1)) ^ cv_swz_tr(r);
-      fa[i] = (uint32_t)(h * CV_QSLOT + r * 128 + c * 16 + 8 * (fi & 1));
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = (2 * j + ((fi >> 1) & 1)) ^ cv_swz_tr(r);
-      fx[j] = (uint32_t)(wn * CV_QSLOT + r * 128 + c * 16 + 8 * (fi & 1));
-    }
-    f32x4 acc[FM][4];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    auto tr8 = [&](uint32_t addr) {
-      lds_i16x4 *p = (lds_i16x4 *)(uintptr_t)addr;
-      const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p);
-      const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p + 4 * 128 / 8);
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-    bf16x8 dv[2][FM], xv[2][4];
-    auto read = [&](uint32_t ds, uint32_t xs, int s, bf16x8 (&dd)[FM], bf16x8 (&xd)[4]) {
-#pragma unroll
-      for (int i = 0; i < FM; ++i) dd[i] = tr8(ds + fa[i] + (uint32_t)(s * 4096));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) xd[j] = tr8(xs + fx[j] + (uint32_t)(s * 4096));
-    };
-    // One 32-k step: its 32 MFMAs in eight groups (row block g against the four column
-    // blocks), with the next step's twelve fragments (24 transpose reads) read two per group
-    // in the first six, the column blocks and the first row blocks first (the next step's
-    // first groups use them). Reading all 24 ahead of the MFMAs made every step wait for ten
-    // of them: the LDS counter tracks at most 15 operations, so the wait that the older
-    // fragments need also covers the oldest of the new reads. The last two groups' MFMAs
-    // cover the reads before the next step or the slab barrier.
-    auto step = [&](const bf16x8 (&df)[FM], const bf16x8 (&xf)[4], uint32_t dsn, uint32_t xsn, int sn,
-                    bf16x8 (&dd)[FM], bf16x8 (&xd)[4]) {
-#pragma unroll
-      for (int g = 0; g < FM; ++g) {
-        if (g < 6) {
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int f = 2 * g + h;
-            if (f < 4) xd[f] = tr8(xsn + fx[f] + (uint32_t)(sn * 4096));
-            else dd[f - 4] = tr8(dsn + fa[f - 4] + (uint32_t)(sn * 4096));
+          for (int q = 0; q < N; ++q) {
+            const uint32_t skip = (uint32_t)cv_div(h0 + cv_div(w0 + row(q), invwp), invh) * (uint32_t)(2 * Wp) * x2;
+            dma16(rx, base[q] != OOB && row(q) < rows ? base[q] + xP + skip : OOB,
+                  slot + (uint32_t)(DSLOT + (w2 + 2 * q) * 1024));
           }
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[g][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[g], xf[j], acc[g][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+        next();
+      };
+      switch ((a.xblk + 1 - w2) / 2) {  // 11 to 16 blocks
+        case 8: run(CvInt<8>{}, issue); break;
+        case 7: run(CvInt<7>{}, issue); break;
+        case 6: run(CvInt<6>{}, issue); break;
+        default: run(CvInt<5>{}, issue);
       }
-    };
-    uint32_t ds = ldsd, xs = ldsx;
-    if (nsl > 0) {
-      lds_barrier();  // B_0
-      read(ds, xs, 0, dv[0], xv[0]);
     }
+    vm_barrier<0>();  // every load landed
+    if constexpr (WK == 2) lds_barrier();
+    return;
+  }
+
+  // ---- MMA waves. A fragment's lane reads cover rows lane/4 and lane/4 + 16 of a 32-position
+  // step (the lane's eight k are four consecutive rows of each, in both operands).
+  const int fi = lane & 15, kg = lane >> 4;
+  const int kh = WK == 2 ? wave >> 2 : 0;
+  const int wo = WK == 2 ? wave & 1 : wave & 3, wc = WK == 2 ? (wave >> 1) & 1 : wave >> 2;
+  const bool live = o0 + 64 * wo < a.Co;
+  const int R = 32 * kh + (lane >> 2);
+  uint32_t fd[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    fd[i] = (uint32_t)(wo * CV_QSLOT + R * 128 + ((32 * i) ^ (16 * cw_swz(R))) + 8 * (lane & 3));
+  auto tr8 = [&](uint32_t p0, uint32_t p1) {
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(uintptr_t)p0);
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(uintptr_t)p1);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  f32x4 acc[6][4];  // [tap column, 16-channel block][output-channel block]
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 xv[6], dv[4];  // fragments, read anew in place as soon as their last MFMA is issued
+  uint32_t rslot = lds0;  // the slab being read
+  // the slab whose fragment rows are being worked out (ahead of the reads), its first
+  // position's column and the positions from there to the end of the range
+  uint32_t aslot = lds0;
+  int aw0 = klo % a.W, acnt = kend - klo;
+  uint32_t ax[2][2];  // activation fragments: set, half of the lane's k
+  const float Rq = ((float)R + 0.5f) * invw, Q16 = 16.0f * invw;
+  const uint32_t xlane = (uint32_t)(DSLOT + 8 * (lane & 3) + 64 * wc);
+  auto set_rows = [&](auto settag, int k) {
+    constexpr int set = decltype(settag)::value;
+    const float q = Rq + (float)aw0 * invw;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int j = R + 32 * k + 16 * h;
+      int u = j + 2 * (int)(q + (float)(2 * k + h) * Q16);
+      if (acnt < 64 && j >= acnt) u = CW_XROWS;  // past the range: a zero row
+      ax[set][h] = (uint32_t)__umul24((uint32_t)u, CW_XPITCH) + (aslot + xlane);
+      asm volatile("" : "+v"(ax[set][h]));  // worked out here, not where it is first used
+    }
+  };
+  auto next_rows = [&]() {
+    aslot = up(aslot);
+    aw0 += a.dw;
+    if (aw0 >= a.W) aw0 -= a.W;
+    acnt -= 64;
+  };
+  auto read_d = [&](int k, int i) {
+    const uint32_t p = rslot + fd[i] + (uint32_t)(4096 * k);
+    dv[i] = tr8(p, p + 2048);
+  };
+  auto read_x = [&](auto settag, int b) {
+    constexpr int set = decltype(settag)::value;
+    const uint32_t d = (uint32_t)(CW_XPITCH * (b >> 1) + 32 * (b & 1));
+    xv[b] = tr8(ax[set][0] + d, ax[set][1] + d);
+  };
+  // One step: the MFMAs of the fragments at hand, and between them the reads of the next step
+  // (k of the slab at rslot, rows in set `nxt`) and the rows of the step after that (kn of
+  // the slab at aslot, into the other set).
+  auto step = [&](auto nxttag, int k, int kn) {
+    constexpr int nxt = decltype(nxttag)::value;
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[b], dv[i], acc[b][i], 0, 0, 0);
+        if (b == 5) {
+          __builtin_amdgcn_sched_barrier(0);
+          read_d(k, i);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      read_x(CvInt<nxt>{}, b);
+      if (b == 1) set_rows(CvInt<nxt ^ 1>{}, kn);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  lds_barrier();  // B_0
+  set_rows(CvInt<0>{}, 0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) read_d(0, i);
+#pragma unroll
+  for (int b = 0; b < 6; ++b) read_x(CvInt<0>{}, b);
+  // (after the last slab the ring's next one, all zeros or spent, is read and not used)
+  if constexpr (WK == 2) {
+    next_rows();
+    set_rows(CvInt<1>{}, 0);
+    for (int S = 0;;) {
+      asm volatile("s_barrier" : : : "memory");  // B_{S+1}
+      rslot = up(rslot);
+      next_rows();
+      step(CvInt<1>{}, 0, 0);
+      if (++S == nsl) break;
+      asm volatile("s_barrier" : : : "memory");
+      rslot = up(rslot);
+      next_rows();
+      step(CvInt<0>{}, 0, 0);
+      if (++S == nsl) break;
+    }
+  } else {
+    set_rows(CvInt<1>{}, 1);
     for (int S = 0; S < nsl; ++S) {
-      step(dv[0], xv[0], ds, xs, 1, dv[1], xv[1]);
+      next_rows();
+      step(CvInt<1>{}, 1, 0);
       lds_barrier();  // B_{S+1}
-      ds = ldsd + (uint32_t)(((S + 1) % CW_ND) * CW_DSLOT);
-      xs = ldsx + (uint32_t)(((S + 1) % CW_NX) * CW_XSLOT);
-      step(dv[1], xv[1], ds, xs, 0, dv[0], xv[0]);  // past the last slab this reads a spent slot, unused
+      rslot = up(rslot);
+      step(CvInt<0>{}, 0, 1);
     }
-    if (nsl == 0) lds_barrier();  // the loaders' B_0 (they pass vm_barrier<0> once)
-    // ---- stage the tile as [output channel][input channel] fp32
-    float *stg = reinterpret_cast<float *>(smem);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          stg[(16 * (8 * wm + i) + 4 * kg + e) * CW_PITCH + 16 * (4 * wn + j) + fi] = acc[i][j][e];
   }
-  lds_barrier();
-  // ---- partial tile out: 256 rows of 128 floats (512 B), device-scope stores
-  const float *stg = reinterpret_cast<const float *>(smem);
-  float *dst = a.partial + (int64_t)split * a.sstride + tap * a.Ci + c0;
-  const __amdgpu_buffer_rsrc_t prs =
-      __builtin_amdgcn_make_buffer_rsrc(dst, 0, (int)(((int64_t)(a.Co - 1) * a.ldp + 128) * 4), BUF_DW3);
-  const int ch = tid & 31, sub = tid >> 5;
+  lds_barrier();  // every load landed, every read done
+  if constexpr (WK == 2) {
+    // the halves' sums through the ring: each gives the other the half of the blocks that the
+    // other writes
+    const uint32_t xs = lds0 + (uint32_t)((wo * 2 + wc) * 24 * 1024 + lane * 16);
+    auto xat = [&](int b, int i) { return (__attribute__((address_space(3))) f32x4 *)(uintptr_t)(xs + (uint32_t)((b * 4 + i) * 1024)); };
+    auto give = [&](auto b0tag) {
+      constexpr int b0 = decltype(b0tag)::value;
 #pragma unroll
-  for (int p = 0; p < 16; ++p) {
-    const int o = 16 * p + sub;
-    const f32x4 v = *reinterpret_cast<const f32x4 *>(stg + o * CW_PITCH + 4 * ch);
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), prs, (uint32_t)((o * a.ldp + 4 * ch) * 4), 0, 16);
+      for (int b = b0; b < b0 + 3; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *xat(b, i) = acc[b][i];
+    };
+    auto take = [&](auto b0tag) {
+      constexpr int b0 = decltype(b0tag)::value;
+#pragma unroll
+      for (int b = b0; b < b0 + 3; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[b][i] += *xat(b, i);
+    };
+    if (kh == 0) give(CvInt<3>{});
+    else give(CvInt<0>{});
+    lds_barrier();
+    if (kh == 0) take(CvInt<0>{});
+    else take(CvInt<3>{});
   }
+  // ---- out: lane (fi, kg) holds channels 4kg .. +3 of output channel fi of each block;
+  // device-scope stores, read next by the reduce
+  if (!live) return;
+  const __amdgpu_buffer_rsrc_t ro =
+      __builtin_amdgcn_make_buffer_rsrc(a.out + (int64_t)split * a.sstride, 0, (int)a.out_bytes, BUF_DW3);
+  const uint32_t ob = (uint32_t)((((o0 + 64 * wo + fi) * 9 + 3 * r3) * a.Ci + c0 + 32 * wc + 4 * kg) * 4);
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    if (WK == 2 && (b / 3) != kh) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[b][i]), ro,
+                                             ob + (uint32_t)((16 * i * 9 + (b >> 1)) * a.Ci * 4 + 64 * (b & 1)), 0, 16);
+  }
+}
+
+// dW = the splits' partials added in split order: four floats a thread, SL slices of the
+// splits per output (each summed in order, then added in slice order), so that many splits of
+// a small dW are still read by enough threads at once.
+template <int SL>
+__global__ void __launch_bounds__(256) conv_wg_reduce(const float *__restrict__ part, int64_t sstride, int splits,
+                                                      int n4, float *__restrict__ out) {
+  constexpr int PER = 256 / SL;
+  const int i = (int)blockIdx.x * PER + (int)threadIdx.x % PER, sl = (int)threadIdx.x / PER;
+  const int s0 = sl * splits / SL, s1 = (sl + 1) * splits / SL;
+  f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (i < n4) {
+    const float *p = part + (int64_t)i * 4;
+#pragma unroll 1
+    for (int s = s0; s < s1; s += 4) {  // four in flight
+      f32x4 q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (s + u < s1) q[u] = *reinterpret_cast<const f32x4 *>(p + (int64_t)(s + u) * sstride);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (s + u < s1) t += q[u];
+    }
+  }
+  if constexpr (SL > 1) {
+    __shared__ f32x4 sums[SL][PER];
+    sums[sl][threadIdx.x % PER] = t;
+    __syncthreads();
+    if (sl != 0) return;
+#pragma unroll
+    for (int v = 1; v < SL; ++v) t += sums[v][threadIdx.x];
+  }
+  if (i < n4) *reinterpret_cast<f32x4 *>(out + (int64_t)i * 4) = t;
 }
 
 }  // namespace
@@ -712,44 +865,93 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
 bool conv_wg_fits(int N, int H, int W, int Ci, int Co, const void *x, const void *dy, const void *dw) {
   if (opt(IMBD_OPT_CONV_NT) == 0) return false;
   auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
-  const int64_t rows = (int64_t)N * (H + 2) * (W + 2) + 2 * (W + 2) + 2 + 64;
-  return N >= 1 && H >= 1 && W >= 1 && Co == 256 && Ci >= 128 && Ci % 128 == 0 && al(x) && al(dy) && al(dw) &&
-         rows * (Ci > Co ? Ci : Co) * 2 < ((int64_t)1 << 31);
+  // rows of an activation slab: 64 positions touch at most (W + 62) / W + 1 image rows (so
+  // images at least 4 wide); byte offsets within one buffer descriptor; short divisions
+  return N >= 1 && H >= 1 && W >= 1 && Co >= 64 && Co % 64 == 0 && Ci >= 64 && Ci % 64 == 0 && al(x) && al(dy) &&
+         al(dw) && cw_slab_rows(W) <= CW_XROWS && H < 32768 && W < 32768 &&
+         (int64_t)N * (H + 2) * (W + 2) * (Ci > Co ? Ci : Co) * 2 < ((int64_t)1 << 31) &&
+         (int64_t)9 * Ci * Co * 4 < ((int64_t)1 << 31);
 }
 
-void conv_wg_plan(int N, int H, int W, int Ci, int *splits, int *k_split) {
-  const int64_t M = (int64_t)N * H * W;
-  const int tiles = 9 * Ci / 128;
-  int s = 256 / tiles;
-  if (s < 1) s = 1;
-  int ks = (int)((M + s - 1) / s + 63) / 64 * 64;
-  if (ks < 64) ks = 64;
-  *k_split = ks;
-  *splits = (int)((M + ks - 1) / ks);
+namespace {
+// floats from one split's partials to the next (off powers of two)
+int64_t cw_split_stride(int Ci, int Co) { return (int64_t)Co * 9 * Ci + 1088; }
+struct CwPlan {
+  int wo, tco, tiles, splits, k_split;
+};
+// The output channels per workgroup and the K splits with the least modelled time: a slab
+// takes about 0.55 us with 128 output channels and 0.95 with 256 (measured at 32 x 56 x 56,
+// 256 -> 256: 105 us on 10 splits with the former, 108 on 21 with the latter), and the partials of every split are written and read once at about 4.5 TB/s
+// together with the reduce's launch (4 us). Only as many splits as ws_bytes holds partials of.
+CwPlan cw_plan(int64_t M, int Ci, int Co, size_t ws_bytes) {
+  CwPlan best{};
+  double least = 0;
+  for (int wo : {2, 4}) {
+    if (wo == 4 && Co % 256 != 0) continue;
+    const int tco = (Co + 64 * wo - 1) / (64 * wo), tiles = tco * 3 * (Ci / 64);
+    const int64_t slabs = (M + 63) / 64;
+    const int most = (int)std::min<int64_t>(std::max(1, CV_CUS / tiles), (slabs + 3) / 4);
+    for (int s = 1; s <= most; ++s) {
+      if (s > 1 && (size_t)s * (size_t)cw_split_stride(Ci, Co) * sizeof(float) > ws_bytes) break;
+      const int64_t per = (slabs + s - 1) / s;
+      const double rounds = (double)((tiles * s + CV_CUS - 1) / CV_CUS);
+      double t = rounds * (double)per * (wo == 2 ? 0.55 : 0.95);
+      if (s > 1) t += 4.0 + 2.0 * s * Co * 9 * Ci * 4 / 4.5e6;
+      if (best.splits == 0 || t < least) {
+        least = t;
+        best = CwPlan{wo, tco, tiles, (int)((slabs + per - 1) / per), (int)(per * 64)};
+      }
+    }
+  }
+  return best;
+}
+}  // namespace
+
+size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co) {
+  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, SIZE_MAX);
+  return pl.splits > 1 ? (size_t)pl.splits * (size_t)cw_split_stride(Ci, Co) * sizeof(float) : 0;
 }
 
-int run_conv_wg(int N, int H, int W, int Ci, int Co, const void *x, const void *dy_pad, float *partial,
-                int64_t ldp, int64_t sstride, hipStream_t s) {
+int run_conv_wg(int N, int H, int W, int Ci, int Co, const void *x, const void *dy_pad, float *dw, void *ws,
+                size_t ws_bytes, hipStream_t s) {
+  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, ws ? ws_bytes : 0);
   CwArgs a;
   a.x = reinterpret_cast<const uint16_t *>(x);
-  a.dy = reinterpret_cast<const uint16_t *>(dy_pad) + (int64_t)(W + 3) * Co;
-  a.partial = partial;
-  a.ldp = ldp;
-  a.sstride = sstride;
+  a.dy = reinterpret_cast<const uint16_t *>(dy_pad);
+  a.out = pl.splits > 1 ? reinterpret_cast<float *>(ws) : dw;
+  a.sstride = pl.splits > 1 ? cw_split_stride(Ci, Co) : 0;
+  a.x_bytes = (uint32_t)((int64_t)N * (H + 2) * (W + 2) * Ci * 2);
+  a.dy_bytes = (uint32_t)((int64_t)N * (H + 2) * (W + 2) * Co * 2);
+  a.out_bytes = (uint32_t)((int64_t)Co * 9 * Ci * 4);
   a.H = H;
   a.W = W;
   a.Ci = Ci;
   a.Co = Co;
   a.M = N * H * W;
-  a.Mp = (int)((int64_t)(N - 1) * (H + 2) * (W + 2) + (int64_t)(H - 1) * (W + 2) + W);
-  conv_wg_plan(N, H, W, Ci, &a.splits, &a.k_split);
-  a.tiles = 9 * Ci / 128;
+  a.k_split = pl.k_split;
+  a.splits = pl.splits;
+  a.tiles = pl.tiles;
+  a.tco = pl.tco;
+  a.xblk = (cw_slab_rows(W) * 10 + 63) / 64;
+  a.dh = 64 / W;
+  a.dw = 64 % W;
   const int grid = (a.tiles * a.splits + 7) / 8 * 8;
   {
     LaunchTimer t(IMBD_K_CONV_WGRAD, 0, s);
-    hipLaunchKernelGGL(conv_wg_kernel, dim3(grid), dim3(512), 0, s, a);
+    if (pl.wo == 2) hipLaunchKernelGGL((conv_wg_kernel<2, 2>), dim3(grid), dim3(768), 0, s, a);
+    else hipLaunchKernelGGL((conv_wg_kernel<4, 1>), dim3(grid), dim3(768), 0, s, a);
   }
-  return check_launch("conv_wg");
+  const int rc = check_launch("conv_wg");
+  if (rc != IMBD_OK || pl.splits == 1) return rc;
+  {
+    LaunchTimer t(IMBD_K_SPLITK, 0, s);
+    const int n4 = Co * 9 * Ci / 4;
+    if (pl.splits <= 8)
+      hipLaunchKernelGGL(conv_wg_reduce<1>, dim3((n4 + 255) / 256), dim3(256), 0, s, a.out, a.sstride, pl.splits, n4, dw);
+    else
+      hipLaunchKernelGGL(conv_wg_reduce<4>, dim3((n4 + 63) / 64), dim3(256), 0, s, a.out, a.sstride, pl.splits, n4, dw);
+  }
+  return check_launch("conv_wg_reduce");
 }
 
 int run_conv_nt(int pass, int N, int H, int W, int Ci, int Co, const void *act, const void *w, void *out,

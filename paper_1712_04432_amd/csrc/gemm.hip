@@ -140,7 +140,7 @@ struct TrLoader {
           bool inside = true;
           if constexpr (KM) {
             int w = wpos + j, h = hpos;
-            if (w >= km.wp) {  // VEC < wp: at most one wrap into the next grid row
+            while (w >= km.wp) {  // wraps into the next grid rows (more than one in narrow grids)
               w -= km.wp;
               h = (h + 1 == km.hp) ? 0 : h + 1;
             }
@@ -1133,13 +1133,18 @@ size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co) {
   if (Ci % 64 || Co % 64) return 0;
   size_t b = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
   if (N >= 1 && conv_wg_fits(N, H, W, Ci, Co, nullptr, nullptr, nullptr)) {
-    // the large-tile kernel's split partials (it always goes through them)
-    int splits, k_split;
-    conv_wg_plan(N, H, W, Ci, &splits, &k_split);
-    const size_t w = (size_t)splits * (size_t)partial_split_stride(9 * Ci, Co) * sizeof(float);
+    // the large-tile kernel's split partials
+    const size_t w = conv_wg_ws_bytes(N, H, W, Ci, Co);
     if (w > b) b = w;
   }
   return b;
+}
+
+size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co) {
+  if (Ci % 64 || Co % 64 || N < 1) return 0;
+  const size_t b = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
+  // the large-tile kernel takes as many splits as fit
+  return conv_wg_fits(N, H, W, Ci, Co, nullptr, nullptr, nullptr) ? std::min(b, conv_wg_ws_bytes(N, H, W, Ci, Co)) : b;
 }
 
 static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void *A, const void *B, void *out,
@@ -1150,37 +1155,19 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
   }
   if (pass != 3 && conv_nt_fits(pass, N, H, W, Ci, Co, B, A, out))
     return run_conv_nt(pass, N, H, W, Ci, Co, B, A, out, out_dtype, s);
-  if (pass == 3 && conv_wg_fits(N, H, W, Ci, Co, A, B, out)) {
-    int splits, k_split;
-    conv_wg_plan(N, H, W, Ci, &splits, &k_split);
-    KArgs g{};
-    g.M = 9 * Ci;
-    g.N = Co;
-    g.splits = splits;
-    g.partial = reinterpret_cast<float *>(ws);
-    g.ldp = partial_ld(g.M);
-    g.sstride = partial_split_stride(g.M, g.N);
-    g.epi = Epilogue{};
-    g.epi.mode = EPI_STORE;
-    g.epi.out = out;
-    g.epi.out_dtype = IMBD_F32;
-    g.epi.ldo = 9 * Ci;
-    const size_t need = (size_t)splits * (size_t)g.sstride * sizeof(float);
-    if (ws == nullptr || ws_bytes < need || (uintptr_t)ws % 16) {
-      set_error("conv weight gradient needs %zu bytes of 16-byte aligned workspace, got %zu", need, ws_bytes);
+  if (pass == 3) {
+    const size_t least = conv_wgrad_ws_least(N, H, W, Ci, Co);
+    if (least > 0 && (ws == nullptr || ws_bytes < least || (uintptr_t)ws % 16)) {
+      set_error("conv weight gradient needs %zu bytes of 16-byte aligned workspace, got %zu", least, ws_bytes);
       return IMBD_EWORKSPACE;
     }
-    {
-      const int rc = run_conv_wg(N, H, W, Ci, Co, A, B, g.partial, g.ldp, g.sstride, s);
-      if (rc != IMBD_OK) return rc;
+    if ((uintptr_t)ws % 16) {  // a workspace that is not needed: none
+      ws = nullptr;
+      ws_bytes = 0;
     }
-    {
-      LaunchTimer t(IMBD_K_SPLITK, 0, s);
-      const dim3 grid((unsigned)((g.M / 8 + 255) / 256), (unsigned)g.N);
-      hipLaunchKernelGGL((splitk_reduce_fast<false, false>), grid, dim3(256), 0, s, g);
-    }
-    return check_launch("conv3x3 reduce");
   }
+  if (pass == 3 && conv_wg_fits(N, H, W, Ci, Co, A, B, out))
+    return run_conv_wg(N, H, W, Ci, Co, A, B, reinterpret_cast<float *>(out), ws, ws_bytes, s);
   const ConvPlan pl = conv_plan(pass, N, H, W, Ci, Co);
   if ((int64_t)N * (H + 2) * (W + 2) * (Ci > Co ? Ci : Co) >= ((int64_t)1 << 31)) {
     set_error("conv tile too large for 32-bit element offsets");

@@ -277,14 +277,14 @@ def test_conv_errors(imbd, dev):
     (1, 5, 7, 512, 448), (7, 13, 13, 192, 384)])
 @pytest.mark.parametrize("out_bf16", [False, True])
 def test_conv_tile_every_channel_count_sampled(imbd, dev, N, H, W, Ci, Co, out_bf16):
-    """Forward and input gradient for channel counts that are multiples of 64:
+    """Forward, input gradient and weight gradient for channel counts that are multiples of 64:
     the layouts of the MMA waves, tile heights and slab pieces that the sizes above name. All
     channels of the first, a middle and the last position and random outputs elsewhere."""
     import torch
     _flush(f"conv channels {(N, H, W, Ci, Co)} bf16={out_bf16}")
     d = make_conv_inputs(N, H, W, Ci, Co, seed=N * 1000 + W, border=(True, False, False, True))
     xv, wv, dyv = bf16_values(d["x_bits"]), bf16_values(d["w_bits"]), bf16_values(d["dy_bits"])
-    y, dx, _ = _run(imbd, dev, d, out_bf16=out_bf16)
+    y, dx, dw = _run(imbd, dev, d, out_bf16=out_bf16)
     rng = np.random.default_rng(W)
     M = N * H * W
     rows = np.unique([0, min(16, M - 1), M // 2, M - 1])
@@ -293,3 +293,48 @@ def test_conv_tile_every_channel_count_sampled(imbd, dev, N, H, W, Ci, Co, out_b
         idx = np.concatenate([(rows[:, None] * C + np.arange(C)[None, :]).reshape(-1), rng.integers(0, M * C, 300)])
         assert nrm_err(host(got).reshape(-1)[idx], at(a, wv, idx)) < tol
         assert torch.isfinite(got).all().item()
+    wi = np.concatenate([rng.integers(0, dw.numel(), 40), [0, dw.numel() - 1]])
+    assert nrm_err(host(dw).reshape(-1)[wi], oracle.conv3x3_wgrad_at(xv, dyv, wi)) < 1e-5
+    assert torch.isfinite(dw).all().item()
+
+
+@pytest.mark.parametrize("N,H,W,Ci,Co", [(3, 20, 20, 64, 256), (2, 9, 3, 64, 64), (5, 31, 17, 128, 384)])
+def test_conv_wgrad_splits_that_fit(imbd, dev, N, H, W, Ci, Co):
+    """The weight gradient with the workspace that its size query names, with half of that (fewer
+    K splits) and, where that is accepted, with none (one range that writes dW itself)."""
+    import torch
+    d = make_conv_inputs(N, H, W, Ci, Co, seed=3)
+    ref = oracle.conv3x3_wgrad(bf16_values(d["x_bits"]), bf16_values(d["dy_bits"]))
+    x, dy = dev_bf16_bits(d["x_bits"], dev), dev_bf16_bits(d["dy_bits"], dev)
+    n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
+    taken = 0
+    for nbytes in (n, n // 2, 0):
+        dw = torch.full((Co, 3, 3, Ci), float("nan"), device=dev)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev) if nbytes else None
+        try:
+            imbd.conv3x3_tile_wgrad(x, dy, dw, ws=ws)
+        except imbd.ImbdError as e:
+            assert e.status == imbd.IMBD_EWORKSPACE and nbytes < n
+            continue
+        torch.cuda.synchronize()
+        taken += 1
+        assert nrm_err(host(dw), ref) < 1e-5
+    assert taken >= 1
+
+
+def test_conv_wgrad_infinity_stays_in_its_rows(imbd, dev):
+    """An infinity in the corner of the halo, in a column that only the last position's tap (2, 2)
+    reads, reaches that tap's gradients and no other: 5 x 13 positions are a slab of 64 and one
+    of a single position, whose other 63 rows must not read it."""
+    import torch
+    N, H, W, Ci, Co = 1, 5, 13, 64, 64
+    d = make_conv_inputs(N, H, W, Ci, Co, seed=8)
+    x, dy = dev_bf16_bits(d["x_bits"], dev), dev_bf16_bits(d["dy_bits"], dev)
+    x[0, H + 1, W + 1, 7] = float("inf")  # read by tap (2, 2) of the last position alone
+    n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
+    dw = torch.zeros((Co, 3, 3, Ci), device=dev)
+    imbd.conv3x3_tile_wgrad(x, dy, dw, ws=torch.empty(max(n, 16), dtype=torch.uint8, device=dev))
+    bad = ~torch.isfinite(dw)
+    assert bad[:, 2, 2, 7].all().item()
+    bad[:, 2, 2, 7] = False
+    assert not bad.any().item()
