@@ -1140,13 +1140,6 @@ size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co) {
   return b;
 }
 
-size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co) {
-  if (Ci % 64 || Co % 64 || N < 1) return 0;
-  const size_t b = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
-  // the large-tile kernel takes as many splits as fit
-  return conv_wg_fits(N, H, W, Ci, Co, nullptr, nullptr, nullptr) ? std::min(b, conv_wg_ws_bytes(N, H, W, Ci, Co)) : b;
-}
-
 static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void *A, const void *B, void *out,
                        int out_dtype, void *ws, size_t ws_bytes, hipStream_t s) {
   if (Ci % 64 || Co % 64) {
@@ -1156,7 +1149,9 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
   if (pass != 3 && conv_nt_fits(pass, N, H, W, Ci, Co, B, A, out))
     return run_conv_nt(pass, N, H, W, Ci, Co, B, A, out, out_dtype, s);
   if (pass == 3) {
-    const size_t least = conv_wgrad_ws_least(N, H, W, Ci, Co);
+    // the template's partials are the least that a call has to bring; the large-tile kernel
+    // takes as many splits as fit into what it is given
+    const size_t least = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
     if (least > 0 && (ws == nullptr || ws_bytes < least || (uintptr_t)ws % 16)) {
       set_error("conv weight gradient needs %zu bytes of 16-byte aligned workspace, got %zu", least, ws_bytes);
       return IMBD_EWORKSPACE;
