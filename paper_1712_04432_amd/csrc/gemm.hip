@@ -42,11 +42,17 @@ template <typename T> struct Elem;
 template <> struct Elem<uint16_t> { static constexpr int VEC = 8; };  // bf16 bit patterns
 template <> struct Elem<float> { static constexpr int VEC = 4; };
 
+// Vectors at any element address: global memory takes 8- and 16-byte accesses at any
+// 2-byte (bf16) or 4-byte (fp32) aligned address in one instruction.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+
 // 16 bytes = VEC consecutive elements starting at p; elements at index >= valid read as 0.
 template <typename T>
-__device__ __forceinline__ u32x4 load16(const T *p, int valid, bool vec_ok) {
+__device__ __forceinline__ u32x4 load16(const T *p, int valid) {
   constexpr int VEC = Elem<T>::VEC;
-  if (valid >= VEC && vec_ok) return *reinterpret_cast<const u32x4 *>(p);
+  if (valid >= VEC) return *reinterpret_cast<const u32x4_any *>(p);
   T tmp[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) tmp[e] = (e < valid) ? p[e] : T(0);
@@ -60,18 +66,29 @@ struct KMask {
   int wp = 1, hp = 1, w = 1, h = 1;
 };
 
+// The loaders' fast path (G = false) loads whole vectors from clamped addresses and keeps a
+// bit per vector that says whether it counts; the others are zeroed when they are stored to
+// LDS. (Zeroed at the load, the compiler moved the selects of the newest loads in front of
+// the older stage's stores, so that every second K tile waited for its own loads. The fp32
+// 9216-4096-4096-1000 step at 256 samples: 800 -> 758 us, with its short weight gradient
+// whole. With the vector loads at any address in the place of element loads, the bf16
+// 4095-1023-517-101 forward and backward at 200 samples: 246 -> 155 us.)
+
 // Operand with k contiguous in memory: the tile is R rows x 128 bytes, 8 chunks per row.
 template <typename T, int R, int NT>
 struct KcLoader {
   static constexpr int VEC = Elem<T>::VEC;
   static constexpr int CH = R * 8;
   static constexpr int PER = (CH + NT - 1) / NT;
+  static constexpr uint32_t ALL = (1u << PER) - 1;
   u32x4 v[PER];
+  uint32_t ok;
 
-  // G: guarded (edge tile: masked, possibly unaligned); !G: interior tile, plain loads
+  // G: guarded (masked element by element); !G: whole chunks (kend is a multiple of VEC)
   template <bool G, bool KM = false>
   __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int rows, int k0,
-                                       int kend, bool vec_ok, int tid, KMask = KMask{}) {
+                                       int kend, int tid, KMask = KMask{}) {
+    ok = ALL;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * NT;
@@ -81,19 +98,21 @@ struct KcLoader {
         const int kk = k0 + kc * VEC;
         if constexpr (G) {
           const int valid = (grow < rows) ? (kend - kk) : 0;
-          v[i] = load16<T>(base + (int64_t)grow * ld + kk, valid, vec_ok);
+          v[i] = load16<T>(base + (int64_t)grow * ld + kk, valid);
         } else {
-          // fast path: chunks are whole (kend % VEC == 0); out-of-range chunks load a
-          // clamped in-range address and are zeroed, without a branch
-          const bool ok = grow < rows && kk < kend;
           const T *p = base + (int64_t)min(grow, rows - 1) * ld + min(kk, kend - VEC);
-          const u32x4 x = *reinterpret_cast<const u32x4 *>(p);
-          v[i] = ok ? x : u32x4{0u, 0u, 0u, 0u};
+          v[i] = *reinterpret_cast<const u32x4_any *>(p);
+          if (!(grow < rows && kk < kend)) ok &= ~(1u << i);
         }
       }
     }
   }
-  __device__ __forceinline__ void store(char *lds, int tid) const {
+  __device__ __forceinline__ void store(char *lds, int tid) {
+    if (ok != ALL) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+        if (!(ok >> i & 1u)) v[i] = u32x4{0u, 0u, 0u, 0u};
+    }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * NT;
@@ -114,13 +133,16 @@ struct TrLoader {
   static constexpr int VEC = Elem<T>::VEC;
   static constexpr int NB = 8 * (R / VEC);
   static constexpr int PER = (NB + NT - 1) / NT;
+  static constexpr uint32_t ALL = (uint32_t)((1ull << (PER * VEC)) - 1);
   u32x4 v[PER][VEC];
+  uint32_t ok;
 
   // KM: k indexes positions of a zero-padded (hp x wp) image grid; rows whose position
   // falls outside the inner (h x w) image read as zero.
   template <bool G, bool KM = false>
   __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int rows, int k0,
-                                       int kend, bool vec_ok, int tid, KMask km = KMask{}) {
+                                       int kend, int tid, KMask km = KMask{}) {
+    ok = ALL;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int blk = tid + i * NT;
@@ -148,20 +170,26 @@ struct TrLoader {
           }
           if constexpr (G) {
             const int valid = (k < kend && inside) ? (rows - col) : 0;
-            v[i][j] = load16<T>(base + (int64_t)k * ld + col, valid, vec_ok);
+            v[i][j] = load16<T>(base + (int64_t)k * ld + col, valid);
           } else {
-            // fast path: rows % VEC == 0, so a chunk is whole or entirely out of range;
-            // out-of-range rows/columns load a clamped address and are zeroed
-            const bool ok = inside && k < kend && col < rows;
-            const T *p = base + (int64_t)min(k, kend - 1) * ld + min(col, rows - VEC);
-            const u32x4 x = *reinterpret_cast<const u32x4 *>(p);
-            v[i][j] = ok ? x : u32x4{0u, 0u, 0u, 0u};
+            // (rows >= VEC. A last chunk that goes past `rows` reads on into the next k-row,
+            // which the caller says exists; it feeds only outputs that are not stored.)
+            const T *p = base + (int64_t)min(k, kend - 1) * ld + (col < rows ? col : 0);
+            v[i][j] = *reinterpret_cast<const u32x4_any *>(p);
+            if (!(inside && k < kend && col < rows)) ok &= ~(1u << (i * VEC + j));
           }
         }
       }
     }
   }
-  __device__ __forceinline__ void store(char *lds, int tid) const {
+  __device__ __forceinline__ void store(char *lds, int tid) {
+    if (ok != ALL) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j)
+          if (!(ok >> (i * VEC + j) & 1u)) v[i][j] = u32x4{0u, 0u, 0u, 0u};
+    }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int blk = tid + i * NT;
@@ -211,7 +239,6 @@ struct KArgs {
   int64_t lda, ldb;
   int M, N, K;
   int k_split, splits, tiles_m, tiles_n;
-  int a_vec, b_vec, out_vec, mask_vec, bias_vec;
   Epilogue epi;
   float *partial;  // [splits][sstride] of [N][ldp] rows when splits > 1
   int64_t ldp, sstride;
@@ -220,7 +247,6 @@ struct KArgs {
   float *bias;
   float db_alpha, bias_lr;
   int cH, cW, cCi, cCo;  // 3x3 conv tile geometry (conv launches only)
-  int fast_ok;           // operand extents allow the clamped fast path (see the kernel)
 };
 
 // ------------------------------------------------------------------------- epilogue
@@ -238,20 +264,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 __device__ __forceinline__ void epilogue4(const KArgs &g, int m, int n, const float v[4]) {
   const Epilogue &e = g.epi;
   const int cnt = (g.M - m) < 4 ? (g.M - m) : 4;
-  const bool vec = cnt == 4 && g.out_vec;
+  const bool vec = cnt == 4;
   if (e.mode == EPI_SGD) {
     float *w = reinterpret_cast<float *>(e.out) + (int64_t)n * e.ldo + m;
     if (vec) {
-      const f32x4 old = *reinterpret_cast<const f32x4 *>(w);
+      const f32x4 old = *reinterpret_cast<const f32x4_any *>(w);
       f32x4 nw;
 #pragma unroll
       for (int i = 0; i < 4; ++i) nw[i] = fmaf(-e.lr, e.alpha * v[i], old[i]);
-      *reinterpret_cast<f32x4 *>(w) = nw;
+      *reinterpret_cast<f32x4_any *>(w) = nw;
       if (e.out2) {
         u32x2 pk;
         pk[0] = pack_bf16x2(nw[0], nw[1]);
         pk[1] = pack_bf16x2(nw[2], nw[3]);
-        *reinterpret_cast<u32x2 *>(e.out2 + (int64_t)n * e.ldo2 + m) = pk;
+        *reinterpret_cast<u32x2_any *>(e.out2 + (int64_t)n * e.ldo2 + m) = pk;
       }
     } else {
 #pragma unroll
@@ -266,8 +292,8 @@ __device__ __forceinline__ void epilogue4(const KArgs &g, int m, int n, const fl
   }
   float x[4], bias[4] = {0.f, 0.f, 0.f, 0.f}, keep[4] = {1.f, 1.f, 1.f, 1.f};
   if (e.bias) {
-    if (cnt == 4 && g.bias_vec) {
-      const f32x4 b4 = *reinterpret_cast<const f32x4 *>(e.bias + m);
+    if (vec) {
+      const f32x4 b4 = *reinterpret_cast<const f32x4_any *>(e.bias + m);
       bias[0] = b4[0]; bias[1] = b4[1]; bias[2] = b4[2]; bias[3] = b4[3];
     } else {
 #pragma unroll
@@ -276,16 +302,16 @@ __device__ __forceinline__ void epilogue4(const KArgs &g, int m, int n, const fl
     }
   }
   if (e.mask) {
-    if (cnt == 4 && g.mask_vec) {
+    if (vec) {
       const int64_t off = (int64_t)n * e.ldmask + m;
       if (e.mask_dtype == IMBD_BF16) {
-        const u32x2 mk = *reinterpret_cast<const u32x2 *>(reinterpret_cast<const uint16_t *>(e.mask) + off);
+        const u32x2 mk = *reinterpret_cast<const u32x2_any *>(reinterpret_cast<const uint16_t *>(e.mask) + off);
         keep[0] = bf16_to_f32((uint16_t)(mk[0] & 0xffffu)) > 0.f;
         keep[1] = bf16_to_f32((uint16_t)(mk[0] >> 16)) > 0.f;
         keep[2] = bf16_to_f32((uint16_t)(mk[1] & 0xffffu)) > 0.f;
         keep[3] = bf16_to_f32((uint16_t)(mk[1] >> 16)) > 0.f;
       } else {
-        const f32x4 mk = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(e.mask) + off);
+        const f32x4 mk = *reinterpret_cast<const f32x4_any *>(reinterpret_cast<const float *>(e.mask) + off);
 #pragma unroll
         for (int i = 0; i < 4; ++i) keep[i] = mk[i] > 0.f;
       }
@@ -307,7 +333,7 @@ __device__ __forceinline__ void epilogue4(const KArgs &g, int m, int n, const fl
       u32x2 pk;
       pk[0] = pack_bf16x2(x[0], x[1]);
       pk[1] = pack_bf16x2(x[2], x[3]);
-      *reinterpret_cast<u32x2 *>(o) = pk;
+      *reinterpret_cast<u32x2_any *>(o) = pk;
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -316,7 +342,7 @@ __device__ __forceinline__ void epilogue4(const KArgs &g, int m, int n, const fl
   } else {
     float *o = reinterpret_cast<float *>(e.out) + (int64_t)n * e.ldo + m;
     if (vec) {
-      *reinterpret_cast<f32x4 *>(o) = f32x4{x[0], x[1], x[2], x[3]};
+      *reinterpret_cast<f32x4_any *>(o) = f32x4{x[0], x[1], x[2], x[3]};
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -396,10 +422,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   constexpr int PASSES = BN / RPP;
   static_assert(NT % TPRW == 0 && BN % RPP == 0, "staged epilogue shape");
   const int er = tid / TPRW, ec = (tid % TPRW) * 4;
-  // Staged when the outputs allow 16-byte stores; ragged tiles guard each row and each
-  // group of 4 columns.
-  const bool staged = g.out_vec;
-  const bool sgd_fast = PREFETCH_W && staged && g.splits == 1 && g.epi.mode == EPI_SGD;
+  // (ragged tiles guard each row and each group of 4 columns)
+  const bool sgd_fast = PREFETCH_W && g.splits == 1 && g.epi.mode == EPI_SGD;
   f32x4 wold[PREFETCH_W ? PASSES : 1];
   if constexpr (PREFETCH_W) {
     if (sgd_fast) {
@@ -409,7 +433,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
         const int n = n0 + p * RPP + er;
         const int m = m0 + ec;
         wold[p] = (n < g.N && m + 4 <= g.M)
-                      ? *reinterpret_cast<const f32x4 *>(w + (int64_t)n * g.epi.ldo + m)
+                      ? *reinterpret_cast<const f32x4_any *>(w + (int64_t)n * g.epi.ldo + m)
                       : f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
@@ -432,16 +456,17 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Interior tiles (every row, column and K tile in range, 16-byte aligned operands) run
-  // the main loop with plain vector loads and no branches around them, so the compiler's
-  // wait counts cover exactly the tile being stored (the last iterations re-load the last
-  // tile instead of skipping the load). Edge tiles run it with masked, conditional loads.
-  // Fast path: aligned operands, whole 16-byte chunks (K ends and transposed-operand
-  // widths are multiples of VEC); ragged M/N/K edges are handled by clamped, zeroed loads
-  // and an odd tile count is padded with one all-zero tile.
-  const bool interior = g.a_vec && g.b_vec && nk > 0 && (kend % VEC == 0) &&
-                        (A_KC || g.M % VEC == 0) && (B_KC || g.N % VEC == 0) && g.fast_ok;
-  const int nk_fast = (nk + NSTAGE - 1) / NSTAGE * NSTAGE;
+  // The K tiles run through the fast path (whole vectors from clamped addresses, no branches
+  // around the loads, so the compiler's wait counts cover exactly the tile being stored; the
+  // last iterations re-load the last tile instead of skipping the load, and an odd tile count
+  // is padded with one all-zero tile). Operands at any element alignment take it; where a
+  // chunk can be cut (K ends off a multiple of VEC, a transposed operand whose width is
+  // none), the split's last K tile comes after them with loads masked element by element.
+  const bool fast = nk > 0 && (A_KC || g.M >= VEC) && (B_KC || g.N >= VEC);
+  const bool ragged = ((A_KC || B_KC) && kend % VEC != 0) || (!A_KC && g.M % VEC != 0) || (!B_KC && g.N % VEC != 0);
+  const int nkf = fast ? (ragged ? nk - 1 : nk) : 0;  // K tiles of the fast path
+  const int kend_f = ragged ? kbeg + nkf * BK : kend;
+  const int nk_fast = (nkf + NSTAGE - 1) / NSTAGE * NSTAGE;
 
   auto compute = [&](int kt) {
     const char *sa = smem + (kt & 1) * STAGE;
@@ -455,24 +480,29 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
 #pragma unroll
       for (int j = 0; j < FN; ++j)
         fb[j] = *reinterpret_cast<const u32x4 *>(sb + (wn0 + j * 16 + fr) * LDS_PITCH + kk * 64 + fg * 16);
+      if constexpr (sizeof(T) == 2) {
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          if constexpr (sizeof(T) == 2) {
+          for (int j = 0; j < FN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                 __builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0, 0);
-          } else {
-            // the whole 16-byte fragment is reinterpreted once; element-wise casts of a
-            // vector lane were lowered to a single repeated lane
-            const f32x4 af = __builtin_bit_cast(f32x4, fa[i]);
-            const f32x4 bf = __builtin_bit_cast(f32x4, fb[j]);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.x, bf.x, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.y, bf.y, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.z, bf.z, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.w, bf.w, acc[i][j], 0, 0, 0);
-          }
-        }
+      } else {
+        // the four k of a fragment one after another over all blocks, so that the sums of one
+        // block (each product waits for the one before) are FM * FN products apart
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+              // the whole 16-byte fragment is reinterpreted once; element-wise casts of a
+              // vector lane were lowered to a single repeated lane
+              const f32x4 af = __builtin_bit_cast(f32x4, fa[i]);
+              const f32x4 bf = __builtin_bit_cast(f32x4, fb[j]);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[e], bf[e], acc[i][j], 0, 0, 0);
+            }
+      }
     }
     if (do_db) {
       // this thread's share of row tid/TPR of the B tile, in k order
@@ -515,86 +545,83 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   }
   auto issueA = [&](auto &L, int kt, auto gtag) {
     constexpr bool G = decltype(gtag)::value;
-    const int kg = kbeg + kt * BK;
+    const int kg = kbeg + kt * BK, kend_g = G ? kend : kend_f;
     if constexpr (CONV == 2) {
       // W[o][tap][c] read as A(c, o) for one tap; a tile past the K range reads nothing
-      const bool live = kg < kend;
+      const bool live = kg < kend_g;
       const int rs = live ? kg / g.cCo : 0, o0 = live ? kg - rs * g.cCo : g.cCo;
-      L.template load<G>(A + (int64_t)rs * g.cCi, g.lda, m0, g.M, o0, g.cCo, g.a_vec, tid);
+      L.template load<G>(A + (int64_t)rs * g.cCi, g.lda, m0, g.M, o0, g.cCo, tid);
     } else {
-      L.template load<G>(A_rs, g.lda, m0, g.M, kg, kend, g.a_vec, tid);
+      L.template load<G>(A_rs, g.lda, m0, g.M, kg, kend_g, tid);
     }
   };
   auto issueB = [&](auto &L, int kt, auto gtag) {
     constexpr bool G = decltype(gtag)::value;
-    const int kg = kbeg + kt * BK;
+    const int kg = kbeg + kt * BK, kend_g = G ? kend : kend_f;
     if constexpr (CONV == 1) {
       // x_pad shifted by tap (r, s): B(c, P) = x_pad_flat[P + r*Wp + s][c]
-      const bool live = kg < kend;
+      const bool live = kg < kend_g;
       const int rs = live ? kg / g.cCi : 0, c0 = live ? kg - rs * g.cCi : g.cCi, r = rs / 3, sx = rs - 3 * r;
-      L.template load<G>(Bp + (int64_t)(r * Wp + sx) * g.cCi, g.ldb, n0, g.N, c0, g.cCi, g.b_vec, tid_b);
+      L.template load<G>(Bp + (int64_t)(r * Wp + sx) * g.cCi, g.ldb, n0, g.N, c0, g.cCi, tid_b);
     } else if constexpr (CONV == 2) {
       // dy_pad shifted by (2-r, 2-s): B(o, P) = dy_pad_flat[P + (2-r)*Wp + 2-s][o]
-      const bool live = kg < kend;
+      const bool live = kg < kend_g;
       const int rs = live ? kg / g.cCo : 0, o0 = live ? kg - rs * g.cCo : g.cCo, r = rs / 3, sx = rs - 3 * r;
-      L.template load<G>(Bp + (int64_t)((2 - r) * Wp + 2 - sx) * g.cCo, g.ldb, n0, g.N, o0, g.cCo, g.b_vec,
-                         tid_b);
+      L.template load<G>(Bp + (int64_t)((2 - r) * Wp + 2 - sx) * g.cCo, g.ldb, n0, g.N, o0, g.cCo, tid_b);
     } else if constexpr (CONV == 3) {
       // interior of dy_pad, rows outside the inner image masked to zero
-      L.template load<G, true>(Bp, g.ldb, n0, g.N, kg, kend, g.b_vec, tid_b, km);
+      L.template load<G, true>(Bp, g.ldb, n0, g.N, kg, kend_g, tid_b, km);
     } else {
-      L.template load<G>(Bp, g.ldb, n0, g.N, kg, kend, g.b_vec, tid_b);
+      L.template load<G>(Bp, g.ldb, n0, g.N, kg, kend_g, tid_b);
     }
   };
   const BoolTag<false> plain{};
   const BoolTag<true> guarded{};
 
-  if (interior) {
-    auto kc = [&](int kt) { return kt; };
+  if (nkf > 0) {
     issueA(la[0], 0, plain);
     issueB(lb[0], 0, plain);
     la[0].store(buf(0), tid);
     lb[0].store(buf(0) + STAGE_A, tid_b);
     if constexpr (NSTAGE == 2) {
-      issueA(la[NSTAGE - 1], kc(1), plain);
-      issueB(lb[NSTAGE - 1], kc(1), plain);
+      issueA(la[NSTAGE - 1], 1, plain);
+      issueB(lb[NSTAGE - 1], 1, plain);
     }
     __syncthreads();
     for (int kt = 0; kt < nk_fast; kt += NSTAGE) {
       if constexpr (NSTAGE == 2) {
         // step kt: set 1 holds tile kt+1; set 0 receives tile kt+2
-        issueA(la[0], kc(kt + 2), plain);
-        issueB(lb[0], kc(kt + 2), plain);
+        issueA(la[0], kt + 2, plain);
+        issueB(lb[0], kt + 2, plain);
         compute(kt);
         la[NSTAGE - 1].store(buf(kt + 1), tid);
         lb[NSTAGE - 1].store(buf(kt + 1) + STAGE_A, tid_b);
         __syncthreads();
         // step kt+1: set 0 holds tile kt+2; set 1 receives tile kt+3
-        issueA(la[NSTAGE - 1], kc(kt + 3), plain);
-        issueB(lb[NSTAGE - 1], kc(kt + 3), plain);
+        issueA(la[NSTAGE - 1], kt + 3, plain);
+        issueB(lb[NSTAGE - 1], kt + 3, plain);
         compute(kt + 1);
         la[0].store(buf(kt + 2), tid);
         lb[0].store(buf(kt + 2) + STAGE_A, tid_b);
         __syncthreads();
       } else {
-        issueA(la[0], kc(kt + 1), plain);
-        issueB(lb[0], kc(kt + 1), plain);
+        issueA(la[0], kt + 1, plain);
+        issueB(lb[0], kt + 1, plain);
         compute(kt);
         la[0].store(buf(kt + 1), tid);
         lb[0].store(buf(kt + 1) + STAGE_A, tid_b);
         __syncthreads();
       }
     }
-  } else {
-    // edge tiles: masked loads, one register stage
-    if (nk > 0) {
-      issueA(la[0], 0, guarded);
-      issueB(lb[0], 0, guarded);
-      la[0].store(buf(0), tid);
-      lb[0].store(buf(0) + STAGE_A, tid_b);
-    }
+  }
+  if (nkf < nk) {
+    // the other K tiles (the last one, or all of them): masked loads, one register stage
+    issueA(la[0], nkf, guarded);
+    issueB(lb[0], nkf, guarded);
+    la[0].store(buf(nkf), tid);
+    lb[0].store(buf(nkf) + STAGE_A, tid_b);
     __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
+    for (int kt = nkf; kt < nk; ++kt) {
       const bool more = kt + 1 < nk;
       if (more) {
         issueA(la[0], kt + 1, guarded);
@@ -608,6 +635,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
       __syncthreads();
     }
   }
+  if (nk == 0) __syncthreads();
 
   if (do_db) {
     // combine the TPR consecutive threads of a row (commutative pairwise adds: every
@@ -622,7 +650,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
     }
   }
 
-  if (staged) {
+  {
     // Stage the accumulator tile in LDS as [n][m] (pitch BM+4 floats), then let each group
     // of TPRW threads finish one whole row per pass.
     constexpr int PT = BM + 4;
@@ -655,12 +683,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
           f32x4 nw;
 #pragma unroll
           for (int q = 0; q < 4; ++q) nw[q] = fmaf(-e.lr, e.alpha * a[q], wold[p][q]);
-          *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(e.out) + (int64_t)n * e.ldo + m) = nw;
+          *reinterpret_cast<f32x4_any *>(reinterpret_cast<float *>(e.out) + (int64_t)n * e.ldo + m) = nw;
           if (e.out2) {
             u32x2 pk;
             pk[0] = pack_bf16x2(nw[0], nw[1]);
             pk[1] = pack_bf16x2(nw[2], nw[3]);
-            *reinterpret_cast<u32x2 *>(e.out2 + (int64_t)n * e.ldo2 + m) = pk;
+            *reinterpret_cast<u32x2_any *>(e.out2 + (int64_t)n * e.ldo2 + m) = pk;
           }
           continue;
         }
@@ -668,30 +696,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
       const float v[4] = {a[0], a[1], a[2], a[3]};
       epilogue4(g, m, n, v);
     }
-    return;
   }
-
-  // Accumulator layout of a 16x16 block: lane holds rows 4*(lane/16)..+3 of column lane%16.
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int m = m0 + wm0 + i * 16 + fg * 4;
-      const int n = n0 + wn0 + j * 16 + fr;
-      if (m >= g.M || n >= g.N) continue;
-      const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-      if (g.splits == 1) {
-        int on = n;
-        if constexpr (CONV == 1 || CONV == 2) {
-          on = conv_out_row(g, n);
-          if (on < 0) continue;
-        }
-        epilogue4(g, m, on, v);
-      } else {
-        float *p = g.partial + (int64_t)s * g.sstride + (int64_t)n * g.ldp + m;
-        *reinterpret_cast<f32x4 *>(p) = f32x4{v[0], v[1], v[2], v[3]};
-      }
-    }
 }
 
 // Sum the split partials in split order, then apply the epilogue.
@@ -756,6 +761,7 @@ const TileCfg kCfgs[] = {
     make_cfg<128, 128, 2, 2>(),  // 1: large products
     make_cfg<128, 64, 2, 2>(),   // 2: tall
     make_cfg<64, 128, 2, 2>(),   // 3: wide
+    make_cfg<32, 32, 2, 2>(),    // 4: a few thousand outputs
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 
@@ -786,25 +792,31 @@ static GemmPlan tiled_plan(const GemmProblem &p) {
   else if (p.M >= 128) cfg = 2;
   else if (p.N >= 128) cfg = 3;
   const int ktiles = cdiv(p.K, BK);
-  // A short product whose large tiles cannot fill 256 CUs takes 64 x 64 tiles instead
-  // (splitting its few K tiles could not fill them either).
-  if (cfg != 0 && ktiles < 16 && cdiv(p.M, kCfgs[cfg].bm) * cdiv(p.N, kCfgs[cfg].bn) < 256) cfg = 0;
+  // K splits while there are too few tiles to fill 256 CUs twice, keeping >= 4 K tiles per
+  // split. A product of fewer than 12 K tiles is left whole: the reduce (and for a weight
+  // gradient the bias sums in a launch of their own) costs more than the K tiles it takes
+  // off the chain, 0.4-0.7 us each (4095 x 1023 and 1023 x 517 weight gradients at 200
+  // samples, 4 K tiles: 22 + 11 + 15 us and 12 + 4 + 7 us in two splits).
+  auto splits_for = [&](int tiles) {
+    if (ktiles < 12 || tiles >= 512) return 1;
+    int most = ktiles / 4;
+    if (tiles * most < 128) most = ktiles / 2;  // a handful of tiles: shorter chains
+    return std::max(1, std::min(cdiv(512, tiles), most));
+  };
+  // A product whose large tiles and splits cannot fill 256 CUs takes 64 x 64 tiles (one of
+  // few K tiles also where they could not fill them twice), and where fewer than 128 of those
+  // come together, 32 x 32: a small product's time is its K tiles' chain, which is half as
+  // long per tile (784-256-128-10 at 64 samples, fp32: the step 62 us on 64 x 64 tiles, 45 on
+  // 32 x 32; 69 before, with more splits and their reduces).
+  auto tiles_of = [&](int c) { return cdiv(p.M, kCfgs[c].bm) * cdiv(p.N, kCfgs[c].bn); };
+  if (cfg != 0 && tiles_of(cfg) * splits_for(tiles_of(cfg)) < (ktiles < 12 ? 512 : 256)) cfg = 0;
+  if (cfg == 0 && tiles_of(0) * splits_for(tiles_of(0)) < 128) cfg = 4;
   const int forced = opt(IMBD_OPT_GEMM_CFG);
   if (forced >= 0 && forced < kNumCfgs) cfg = forced;
   pl.cfg = cfg;
   pl.bm = kCfgs[cfg].bm;
   pl.bn = kCfgs[cfg].bn;
-  const int tiles = cdiv(p.M, pl.bm) * cdiv(p.N, pl.bn);
-  // Split K while there are too few tiles to fill 256 CUs twice, keeping >= 4 K tiles
-  // per split (>= 2 for products of 4..15 K tiles); a product of fewer K tiles is left
-  // whole (a second launch would cost more).
-  int splits = 1;
-  if (tiles < 512 && ktiles >= 4) {
-    splits = cdiv(512, tiles);
-    const int max_s = ktiles >= 16 ? ktiles / 4 : ktiles / 2;
-    if (splits > max_s) splits = max_s;
-    if (splits < 1) splits = 1;
-  }
+  int splits = splits_for(tiles_of(cfg));
   const int forced_s = opt(IMBD_OPT_GEMM_SPLITS);
   if (forced_s >= 1) splits = forced_s < ktiles ? forced_s : (ktiles > 0 ? ktiles : 1);
   int k_split = cdiv(cdiv(p.K > 0 ? p.K : 1, splits), BK) * BK;
@@ -1022,7 +1034,6 @@ int gemm_run(const GemmProblem &p, void *ws, size_t ws_bytes, hipStream_t s) {
     if (rc != IMBD_OK) return rc;
   }
   if (pl.cfg == PLAN_SKINNY) return run_skinny(p, ws, s);
-  const int esz = p.dtype == IMBD_BF16 ? 2 : 4;
   KArgs g;
   g.A = p.A;
   g.B = p.B;
@@ -1035,23 +1046,6 @@ int gemm_run(const GemmProblem &p, void *ws, size_t ws_bytes, hipStream_t s) {
   g.splits = pl.splits;
   g.tiles_m = cdiv(p.M, pl.bm);
   g.tiles_n = cdiv(p.N, pl.bn);
-  const int vec_elems = 16 / esz;
-  g.a_vec = ((uintptr_t)p.A % 16 == 0) && (p.lda % vec_elems == 0);
-  g.b_vec = ((uintptr_t)p.B % 16 == 0) && (p.ldb % vec_elems == 0);
-  {
-    const Epilogue &e = p.epi;
-    const int oes = (e.mode == EPI_SGD || e.out_dtype == IMBD_F32) ? 4 : 2;
-    bool ok = ((uintptr_t)e.out % (4 * oes) == 0) && (e.ldo % 4 == 0);
-    if (e.mode == EPI_SGD && e.out2) ok = ok && ((uintptr_t)e.out2 % 8 == 0) && (e.ldo2 % 4 == 0);
-    g.out_vec = ok;
-  }
-  {
-    const Epilogue &e = p.epi;
-    const int mes = e.mask_dtype == IMBD_BF16 ? 2 : 4;
-    g.mask_vec = e.mask && ((uintptr_t)e.mask % (4 * mes) == 0) && (e.ldmask % 4 == 0);
-    g.bias_vec = e.bias && ((uintptr_t)e.bias % 16 == 0);
-  }
-  g.fast_ok = 1;
   g.epi = p.epi;
   g.db_mode = p.db_mode;
   g.db_out = p.db_out;
@@ -1189,10 +1183,6 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
   g.splits = pl.splits;
   g.tiles_m = cdiv(pl.M, pl.bm);
   g.tiles_n = cdiv(pl.N, pl.bn);
-  g.a_vec = g.b_vec = 1;
-  g.out_vec = 1;
-  g.fast_ok = 1;
-  g.mask_vec = g.bias_vec = 0;
   g.epi = Epilogue{};
   g.epi.mode = EPI_STORE;
   g.epi.out = out;

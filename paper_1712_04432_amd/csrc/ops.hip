@@ -92,17 +92,18 @@ __global__ void __launch_bounds__(256)
 }
 
 // db[m] = alpha * sum_b dy[b][m]: 64 columns per workgroup, each column's rows split in
-// 4 contiguous slices summed in ascending b, the slice sums added in slice order;
-// optionally bias[m] -= lr * db[m].
+// 16 contiguous slices (one wave each) summed in ascending b, the slice sums added in slice
+// order; optionally bias[m] -= lr * db[m]. What it takes is a chain of loads per thread, so
+// the slices are short (16 instead of 4 at 1000 x 1023 bf16: 69 -> 22 us).
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
     bias_grad_kernel(int M, int B, const T *__restrict__ dy, int64_t lddy, float alpha,
                      float *__restrict__ db_out, float *__restrict__ bias, float lr) {
-  __shared__ float part[4][64];
+  __shared__ float part[16][64];
   const int col = threadIdx.x & 63, slice = threadIdx.x >> 6;
   const int m = blockIdx.x * 64 + col;
-  const int per = (B + 3) / 4;
-  const int b0 = slice * per, b1 = min(B, b0 + per);
+  const int per = (B + 15) / 16;
+  const int b0 = min(B, slice * per), b1 = min(B, b0 + per);
   float s = 0.f;
   if (m < M) {
     for (int b = b0; b < b1; ++b) {
@@ -114,7 +115,10 @@ __global__ void __launch_bounds__(256)
   part[slice][col] = s;
   __syncthreads();
   if (slice == 0 && m < M) {
-    const float g = alpha * (((part[0][col] + part[1][col]) + part[2][col]) + part[3][col]);
+    float t = part[0][col];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) t += part[k][col];
+    const float g = alpha * t;
     if (db_out) db_out[m] = g;
     if (bias) bias[m] = fmaf(-lr, g, bias[m]);
   }
@@ -253,10 +257,10 @@ int run_bias_grad(int dtype, int M, int B, const void *dy, int64_t lddy, float a
     hipLaunchKernelGGL(bias_grad_wide, dim3((M + 63) / 64), dim3(256), 0, s, M, B,
                        reinterpret_cast<const uint16_t *>(dy), lddy, alpha, db_out, bias_sgd, lr);
   else if (dtype == IMBD_BF16)
-    hipLaunchKernelGGL(bias_grad_kernel<uint16_t>, dim3((M + 63) / 64), dim3(256), 0, s, M, B,
+    hipLaunchKernelGGL(bias_grad_kernel<uint16_t>, dim3((M + 63) / 64), dim3(1024), 0, s, M, B,
                        reinterpret_cast<const uint16_t *>(dy), lddy, alpha, db_out, bias_sgd, lr);
   else
-    hipLaunchKernelGGL(bias_grad_kernel<float>, dim3((M + 63) / 64), dim3(256), 0, s, M, B,
+    hipLaunchKernelGGL(bias_grad_kernel<float>, dim3((M + 63) / 64), dim3(1024), 0, s, M, B,
                        reinterpret_cast<const float *>(dy), lddy, alpha, db_out, bias_sgd, lr);
   return check_launch("bias_grad");
 }

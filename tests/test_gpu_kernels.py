@@ -475,3 +475,49 @@ def test_skinny_every_plan(imbd, dev, nb, splits, shape):
     assert nrm_err(host(dx), oracle.relu_mask(oracle.input_grad(W, DY), X)) < 1e-5
     assert nrm_err(host(dxbig[:, :din]), oracle.input_grad(W, DY)) < 1e-5
     assert torch.all(dxbig[:, din] == 7.0).item()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [
+    # d_out, d_in, b: widths below one vector; K tails of 1..7 in the one K tile and after many;
+    # tiles of 32, 64 and 128 with ragged rows; split K with a ragged last split
+    (5, 7, 3), (9, 33, 17), (37, 101, 13), (130, 203, 70), (517, 1023, 200), (258, 4099, 131), (1031, 259, 263)])
+def test_unaligned_blocks_in_nan_surroundings(imbd, dev, dtype, shape):
+    """Blocks that start at an odd element of arrays with an odd pitch, everything outside them NaN:
+    the tiled template's whole-vector loads at any address, its reads past a ragged row (into
+    the next one) and its ragged last K tile must let none of it into an output, and nothing
+    outside the output blocks may be written."""
+    import torch
+    dout, din, b = shape
+    _flush(f"unaligned {dtype} {shape}")
+    d, W, X, DY = _local_inputs(dout, din, b, dtype, seed=11)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def placed(t):
+        big = torch.full((t.shape[0] + 2, t.shape[1] + 6 + t.shape[1] % 2), float("nan"), dtype=t.dtype, device=dev)
+        v = big[1:-1, 3:3 + t.shape[1]]
+        v.copy_(t)
+        return big, v
+
+    wd, xd, dyd = (placed(_to_dev(d, k, dtype, dev))[1] for k in ("w", "x", "dy"))
+    bias = placed(dev_f32(d["b"].reshape(1, -1), dev))[1].reshape(-1)
+    code = imbd.dtype_code(tdt)
+    tol = 1e-5 if dtype == "bf16" else 2e-6
+    ws = torch.zeros(max(16, *(imbd.mlp_local_workspace_bytes(k, code, dout, din, b) for k in (0, 1))),
+                     dtype=torch.uint8, device=dev)
+    ref = oracle.relu(oracle.affine_fwd(W, X, d["b"].astype(np.float64)))
+    for odt in (torch.float32, torch.bfloat16):
+        ybig, y = placed(torch.zeros((b, dout), dtype=odt, device=dev))
+        imbd.mlp_local_fwd(wd, xd, y, 1, 1, bias=bias, relu=True, ws=ws)
+        torch.cuda.synchronize()
+        assert nrm_err(host(y), ref) < (tol if odt == torch.float32 else 2.0 ** -8 + tol)
+        assert torch.isnan(ybig).sum().item() == ybig.numel() - y.numel()
+    rdw, rdb, rdx = oracle.local_bwd(W, DY, X, 1.0 / (b * 4), mask_src=X)
+    dwbig, dw = placed(torch.zeros((dout, din), device=dev))
+    dxbig, dx = placed(torch.zeros((b, din), device=dev))
+    db = torch.zeros(dout, device=dev)
+    imbd.mlp_local_bwd(wd, dyd, xd, dw, 1, 4, db_part=db, dx_part=dx, mask_relu=True, ws=ws)
+    torch.cuda.synchronize()
+    assert nrm_err(host(dw), rdw) < tol and nrm_err(host(db), rdb) < tol and nrm_err(host(dx), rdx) < tol
+    for big, v in ((dwbig, dw), (dxbig, dx)):
+        assert torch.isnan(big).sum().item() == big.numel() - v.numel()
