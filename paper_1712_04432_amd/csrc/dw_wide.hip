@@ -3,8 +3,7 @@
 //   Delta_W[o][i] = sum_b Delta_Y[b][o] X[b][i]      (Sec. 1, K = the batch)
 //   w[o][i] -= lr * alpha * Delta_W[o][i];  w16[o][i] = bf16(w[o][i])   (Eq. (1))
 // (or, for the unfused and local backward passes, alpha * Delta_W stored as fp32). The
-// bias gradient (column sums of Delta_Y) comes from the workgroups of the first column
-// tile up to 512 samples, else from the column-sum kernel.
+// bias gradient (column sums of Delta_Y) comes from the workgroups of the first column tile.
 //
 // At these batch sizes the product (2 x batch flops per weight) outweighs the update's
 // 10 bytes per weight, so the kernel takes the large-tile layout of the conv tile's
@@ -113,14 +112,12 @@ void dw_wide_prepare(const GemmProblem &p, int extra_blocks, DlArgs *out, int *o
   const int dual_opt = opt(IMBD_OPT_DW_WIDE_DUAL);
   const bool dual = extra_blocks == 0 && (dual_opt == 1 || (dual_opt == -1 && t128 > 256));
   // (4-byte pieces: 128-row tiles, whose loads in flight fit the memory counter)
-  const bool half = dual || p.b_dw4 || ((t128 + 255) / 256) * 128 * 11 < ((t256 + 255) / 256) * 256 * 10;
+  // (one column tile cannot hold the bias sums of 256-row tiles, which take two)
+  const bool half = dual || p.b_dw4 || (p.db_mode != 0 && ti == 1) || ((t128 + 255) / 256) * 128 * 11 < ((t256 + 255) / 256) * 256 * 10;
   const int oh = half ? 128 : 256;
   a.tiles_o = (p.N + oh - 1) / oh;
   a.tiles_i = (p.M + 127) / 128;
-  // the bias gradient in the kernel up to 512 samples (a few microseconds of one column
-  // tile's workgroups); past that the column-sum kernel spreads it over more workgroups
-  const bool db_here = p.db_mode != 0 && p.K <= 512;
-  a.db_mode = db_here ? p.db_mode : 0;
+  a.db_mode = p.db_mode;
   a.db_alpha = p.db_alpha;
   a.bias_lr = p.bias_lr;
   a.db_out = p.db_out;
@@ -159,10 +156,7 @@ int run_dw_wide(const GemmProblem &p, hipStream_t s, const ReduceTail *tail) {
       else hipLaunchKernelGGL((dw_wide_kernel<false, 256, false>), dim3(grid), dim3(512), 0, s, a);
     }
   }
-  int rc = check_launch("dw_wide");
-  if (rc != IMBD_OK || p.db_mode == 0 || a.db_mode != 0) return rc;
-  return run_bias_grad(IMBD_BF16, p.N, p.K, p.B, p.ldb, p.db_alpha, p.db_mode == 1 ? p.db_out : nullptr,
-                       p.db_mode == 2 ? p.bias : nullptr, p.bias_lr, s, p.layer);
+  return check_launch("dw_wide");
 }
 
 }  // namespace imbd

@@ -30,7 +30,7 @@ struct DlArgs {
   float lr, alpha;
   int tiles_o, tiles_i;
   // bias gradient, db[o] = db_alpha * sum_b Delta_Y[b][o], by the workgroups of the first
-  // column tile (db_mode 0: none (a separate launch), 1: store db_out, 2: bias -= bias_lr * db)
+  // column tiles (db_mode 0: none, 1: store db_out, 2: bias -= bias_lr * db)
   int db_mode;
   float db_alpha, bias_lr;
   float *db_out, *bias;
@@ -72,7 +72,7 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
   static_assert(DRING + XRING == dl_lds_bytes<OH, DUAL>(), "LDS size");
   static_assert(!DUAL || OH == 128, "two workgroups per CU: 128-row tiles");
   static_assert(DRING + XRING <= (DUAL ? 80 : 160) * 1024, "LDS");
-  static_assert(OH * DL_PITCH * 4 + 512 * 4 <= DRING + XRING, "staging and bias sums");
+  static_assert(OH * DL_PITCH * 4 <= DRING + XRING, "staging");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -245,11 +245,29 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
 #pragma unroll
       for (int j = 0; j < 4; ++j) xd[j] = tr8(xs + fx[j] + (uint32_t)(s * 4096));
     };
+    // The bias gradient, the row sums of the Delta_Y fragments: in the first column tile (the
+    // first two of 256-row tiles) each wave multiplies two of its row blocks by ones too
+    // (every column of the product is the sum): an eighth (a sixteenth) more MFMAs in one
+    // (two) of a row's many tiles, and eight registers. (Summed from memory by the tile's
+    // threads afterwards, up to 512 samples, or by a launch of its own past them:
+    // 9216-4096-4096-1000 at 2048 samples spent 3 x 9.5 us on those launches.)
+    const bool dodb = it < FM / 4 && a.db_mode != 0;
+    const int ib = (FM == 8 ? 2 * it : 0) + wn;  // the wave's pair of row blocks
+    f32x4 accb[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
     auto mma = [&](const bf16x8 (&df)[FM], const bf16x8 (&xf)[4]) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[i], xf[j], acc[i][j], 0, 0, 0);
+      if (dodb) {
+#pragma unroll
+        for (int q = 0; q < FM / 2; ++q)
+          if (q == ib) {
+            accb[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[2 * q], ones, accb[0], 0, 0, 0);
+            accb[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[2 * q + 1], ones, accb[1], 0, 0, 0);
+          }
+      }
     };
     uint32_t ds = ldsd, xs = ldsx;
     lds_barrier();  // B_0
@@ -280,6 +298,19 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
       }
     }
     if constexpr (EARLY) load_masters();
+    if (dodb && fi == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int o = o0 + 16 * (FM * wm + 2 * ib + i) + 4 * kg + e;
+          if (o < a.N) {
+            const float db = a.db_alpha * accb[i][e];
+            if (a.db_mode == 1) a.db_out[o] = db;
+            else a.bias[o] -= a.bias_lr * db;
+          }
+        }
+    }
     // ---- stage the tile as [o][i] fp32
     float *stg = reinterpret_cast<float *>(smem);
 #pragma unroll
@@ -289,39 +320,6 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           stg[(16 * (FM * wm + i) + 4 * kg + e) * DL_PITCH + 16 * (4 * wn + j) + fi] = acc[i][j][e];
-  }
-  if (it == 0 && a.db_mode != 0) {
-    // ---- bias gradient of the tile's OH rows o: thread t sums column o0 + t%OH over the
-    // samples of its part (t/OH of 512/OH parts) in ascending order, the parts are added
-    // in order. The staged tile leaves LDS free past it.
-    __syncthreads();
-    constexpr int NP = 512 / OH;
-    float *part = reinterpret_cast<float *>(smem + OH * DL_PITCH * 4);
-    const int col = tid % OH, pi = tid / OH, o = o0 + col;
-    const int kh = (a.K + NP - 1) / NP, b0 = min(a.K, pi * kh), b1 = min(a.K, b0 + kh);
-    float sum = 0.f;
-    if (o < a.N) {
-      const uint16_t *p = a.DY + o;
-      int b = b0;
-      for (; b + 8 <= b1; b += 8) {
-        float v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = bf16_to_f32(p[(int64_t)(b + q) * a.lddy]);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) sum += v[q];
-      }
-      for (; b < b1; ++b) sum += bf16_to_f32(p[(int64_t)b * a.lddy]);
-    }
-    part[tid] = sum;
-    __syncthreads();
-    if (tid < OH && o < a.N) {
-      float t = part[tid];
-#pragma unroll
-      for (int q = 1; q < NP; ++q) t += part[tid + q * OH];
-      const float db = a.db_alpha * t;
-      if (a.db_mode == 1) a.db_out[o] = db;
-      else a.bias[o] -= a.bias_lr * db;
-    }
   }
   // ---- the update: thread (sub, ch) takes rows o0 + US*u + sub (u < UR), columns
   // i0 + 4ch .. +3, with all its rows' masters in flight at once. One workgroup per CU: the

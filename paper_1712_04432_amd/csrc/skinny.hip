@@ -800,13 +800,13 @@ int run_local_dx_dw_pair(const GemmProblem &dx, const GemmProblem &dw, void *ws,
   const SkPlan pl = sk_plan(dx);
   if (pl.splits != 1) return NOT_TAKEN;  // its reduce would follow the pair
   if (dx.b_dw4 && pl.nb > 2) return NOT_TAKEN;
-  // the large-tile product alone on two workgroups per CU (a launch of its own is faster)
-  // or with its bias on the column-sum kernel: not paired
+  // the large-tile product alone on two workgroups per CU (a launch of its own is faster):
+  // not paired
   DlArgs d;
   int oh, g_dl;
   bool dual;
   dw_wide_prepare(dw, 0, &d, &oh, &dual, &g_dl);
-  if (dual || (dw.db_mode != 0 && d.db_mode == 0)) return NOT_TAKEN;
+  if (dual) return NOT_TAKEN;
   SkArgs g;
   const int n_sk = prepare_skinny(dx, pl, ws, true, &g);
   const int n_pad = (n_sk + 7) / 8 * 8;
