@@ -13,6 +13,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// Vectors at any element address: global memory takes 8- and 16-byte accesses at any
+// 2-byte (bf16) or 4-byte (fp32) aligned address in one instruction.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 
 // ------------------------------------------------------------------------- bf16 bits
 // fp32 -> bf16, round to nearest, ties to even; NaN stays a (quiet) NaN. Adding

@@ -42,12 +42,6 @@ template <typename T> struct Elem;
 template <> struct Elem<uint16_t> { static constexpr int VEC = 8; };  // bf16 bit patterns
 template <> struct Elem<float> { static constexpr int VEC = 4; };
 
-// Vectors at any element address: global memory takes 8- and 16-byte accesses at any
-// 2-byte (bf16) or 4-byte (fp32) aligned address in one instruction.
-typedef u32x4 u32x4_any __attribute__((aligned(2)));
-typedef u32x2 u32x2_any __attribute__((aligned(2)));
-typedef f32x4 f32x4_any __attribute__((aligned(4)));
-
 // 16 bytes = VEC consecutive elements starting at p; elements at index >= valid read as 0.
 template <typename T>
 __device__ __forceinline__ u32x4 load16(const T *p, int valid) {

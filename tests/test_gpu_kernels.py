@@ -521,3 +521,40 @@ def test_unaligned_blocks_in_nan_surroundings(imbd, dev, dtype, shape):
     assert nrm_err(host(dw), rdw) < tol and nrm_err(host(db), rdb) < tol and nrm_err(host(dx), rdx) < tol
     for big, v in ((dwbig, dw), (dxbig, dx)):
         assert torch.isnan(big).sum().item() == big.numel() - v.numel()
+
+
+@pytest.mark.parametrize("C", [1, 3, 63, 64, 66, 257, 1001, 1021, 1024])
+@pytest.mark.parametrize("B", [5, 300])
+def test_top_layer_softmax_class_counts(imbd, dev, B, C):
+    """The top layer's pass over the split partials (up to 256 samples on the skinny kernel's
+    tiles, past them on the wide kernel's rows), four classes per thread: class counts around a
+    vector, a wave and the last thread, one label in the last class."""
+    import torch
+    from synthdata import make_mlp_inputs, scaled_mlp
+    from tests._util import input_on_device, make_layers, workspace
+    cfg = scaled_mlp((1024, C), B, "bf16")
+    d = make_mlp_inputs(cfg, seed=C)
+    d["labels"][0] = C - 1
+    net = imbd.MLP(cfg.dims, B, "bf16")
+    layers = make_layers(imbd, d, dev, "bf16")
+    x, xv = input_on_device(d, dev, "bf16")
+    ws = workspace(imbd, net, dev)
+    loss = torch.zeros(1, device=dev)
+    imbd.mlp_fwd(net, layers, x, torch.from_numpy(d["labels"]).to(dev), ws, loss)
+    torch.cuda.synchronize()
+    W = oracle.round_bf16(d["w"][0].astype(np.float64))
+    z = oracle.affine_fwd(W, xv, d["b"][0].astype(np.float64))
+    lg = host(imbd.ws_view(net, ws, imbd.IMBD_WS_LOGITS))
+    assert nrm_err(lg, z) < 1e-5
+    zz = lg.astype(np.float64)
+    m = zz.max(axis=1, keepdims=True)
+    e = np.exp(zz - m)
+    s = e.sum(axis=1, keepdims=True)
+    rows = (m + np.log(s))[:, 0] - zz[np.arange(B), d["labels"]]
+    dz = e / s
+    dz[np.arange(B), d["labels"]] -= 1.0
+    # fp32 exp, sums and logarithm of values up to ~10: a few 1e-7 of the row's size
+    assert np.abs(host(imbd.ws_view(net, ws, imbd.IMBD_WS_ROWLOSS)) - rows).max() < 1e-5 * max(1.0, np.abs(zz).max())
+    assert abs(loss.item() - rows.mean()) < 1e-5 * max(1.0, abs(rows.mean()))
+    got = host(imbd.ws_view(net, ws, imbd.IMBD_WS_DY, 1))
+    assert np.abs(got - dz / B).max() <= (2.0 ** -8 + 1e-5) * max(np.abs(dz / B).max(), 1e-30)
