@@ -228,7 +228,9 @@ int run_conv_dgrad(int N, int H, int W, int Ci, int Co, const void *dyp, const v
                    int dx_dtype, hipStream_t s);
 int run_conv_wgrad(int N, int H, int W, int Ci, int Co, const void *xp, const void *dyp,
                    float *dw, void *ws, size_t ws_bytes, hipStream_t s);
+// Workspace for the planned K splits, and the least that a call accepts (fewer splits then).
 size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co);
+size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co);
 // The forward (pass 1) and input-gradient (pass 2) passes on the large-tile implicit-GEMM
 // kernel (channel counts that are multiples of 64): whether it takes the problem, and the launch.
 bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act, const void *w, const void *out);
@@ -238,9 +240,10 @@ int run_conv_nt(int pass, int N, int H, int W, int Ci, int Co, const void *act, 
 // 64, images at least 4 wide): whether it takes the problem, the workspace of its K splits'
 // partials, and the launches.
 bool conv_wg_fits(int N, int H, int W, int Ci, int Co, const void *x, const void *dy, const void *dw);
-size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co);
+// prefer: bytes that the plan stays within unless more splits are clearly faster.
+size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co, size_t prefer);
 int run_conv_wg(int N, int H, int W, int Ci, int Co, const void *x, const void *dy_pad, float *dw, void *ws,
-                size_t ws_bytes, hipStream_t s);
+                size_t ws_bytes, size_t prefer, hipStream_t s);
 
 // --------------------------------------------------------------------- host helpers
 // Current value of an option (enum imbd_option), set at load from the environment or by

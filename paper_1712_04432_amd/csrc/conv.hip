@@ -883,9 +883,10 @@ struct CwPlan {
 // takes about 0.55 us with 128 output channels and 0.95 with 256 (measured at 32 x 56 x 56,
 // 256 -> 256: 105 us on 10 splits with the former, 108 on 21 with the latter), and the partials of every split are written and read once at about 4.5 TB/s
 // together with the reduce's launch (4 us). Only as many splits as ws_bytes holds partials of.
-CwPlan cw_plan(int64_t M, int Ci, int Co, size_t ws_bytes) {
+CwPlan cw_best(int64_t M, int Ci, int Co, size_t ws_bytes, double *time) {
   CwPlan best{};
-  double least = 0;
+  double &least = *time;
+  least = 0;
   for (int wo : {2, 4}) {
     if (wo == 4 && Co % 256 != 0) continue;
     const int tco = (Co + 64 * wo - 1) / (64 * wo), tiles = tco * 3 * (Ci / 64);
@@ -905,16 +906,24 @@ CwPlan cw_plan(int64_t M, int Ci, int Co, size_t ws_bytes) {
   }
   return best;
 }
+// A plan within `prefer` bytes (what the tiled template's splits take) unless a larger
+// workspace is more than a tenth faster.
+CwPlan cw_plan(int64_t M, int Ci, int Co, size_t ws_bytes, size_t prefer) {
+  double t, tp;
+  const CwPlan any = cw_best(M, Ci, Co, ws_bytes, &t);
+  const CwPlan small = cw_best(M, Ci, Co, std::min(ws_bytes, prefer), &tp);
+  return tp <= 1.1 * t ? small : any;
+}
 }  // namespace
 
-size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co) {
-  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, SIZE_MAX);
+size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co, size_t prefer) {
+  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, SIZE_MAX, prefer);
   return pl.splits > 1 ? (size_t)pl.splits * (size_t)cw_split_stride(Ci, Co) * sizeof(float) : 0;
 }
 
 int run_conv_wg(int N, int H, int W, int Ci, int Co, const void *x, const void *dy_pad, float *dw, void *ws,
-                size_t ws_bytes, hipStream_t s) {
-  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, ws ? ws_bytes : 0);
+                size_t ws_bytes, size_t prefer, hipStream_t s) {
+  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, ws ? ws_bytes : 0, prefer);
   CwArgs a;
   a.x = reinterpret_cast<const uint16_t *>(x);
   a.dy = reinterpret_cast<const uint16_t *>(dy_pad);

@@ -791,18 +791,25 @@ static GemmPlan tiled_plan(const GemmProblem &p) {
   // gradient the bias sums in a launch of their own) costs more than the K tiles it takes
   // off the chain, 0.4-0.7 us each (4095 x 1023 and 1023 x 517 weight gradients at 200
   // samples, 4 K tiles: 22 + 11 + 15 us and 12 + 4 + 7 us in two splits).
+  auto tiles_of = [&](int c) { return cdiv(p.M, kCfgs[c].bm) * cdiv(p.N, kCfgs[c].bn); };
+  auto whole_k = [&](int s) { return cdiv(p.K, cdiv(cdiv(p.K, s), BK) * BK); };  // splits that s comes to
+  // (never more of them than 512 workgroups of the largest tiles make: the workspace of a
+  // shape, and with it what fits the library's own scratch, does not grow with smaller tiles)
+  const int lcfg = cfg != 0 && ktiles < 16 && tiles_of(cfg) < 256 ? 0 : cfg, ltiles = tiles_of(lcfg);
+  const int bound = p.K > 0 && ltiles < 512 && ktiles >= 4
+                        ? whole_k(std::max(1, std::min(cdiv(512, ltiles), ktiles >= 16 ? ktiles / 4 : ktiles / 2)))
+                        : 1;
   auto splits_for = [&](int tiles) {
     if (ktiles < 12 || tiles >= 512) return 1;
     int most = ktiles / 4;
     if (tiles * most < 128) most = ktiles / 2;  // a handful of tiles: shorter chains
-    return std::max(1, std::min(cdiv(512, tiles), most));
+    return std::max(1, std::min({cdiv(512, tiles), most, bound}));
   };
   // A product whose large tiles and splits cannot fill 256 CUs takes 64 x 64 tiles (one of
   // few K tiles also where they could not fill them twice), and where fewer than 128 of those
   // come together, 32 x 32: a small product's time is its K tiles' chain, which is half as
   // long per tile (784-256-128-10 at 64 samples, fp32: the step 62 us on 64 x 64 tiles, 45 on
   // 32 x 32; 69 before, with more splits and their reduces).
-  auto tiles_of = [&](int c) { return cdiv(p.M, kCfgs[c].bm) * cdiv(p.N, kCfgs[c].bn); };
   if (cfg != 0 && tiles_of(cfg) * splits_for(tiles_of(cfg)) < (ktiles < 12 ? 512 : 256)) cfg = 0;
   if (cfg == 0 && tiles_of(0) * splits_for(tiles_of(0)) < 128) cfg = 4;
   const int forced = opt(IMBD_OPT_GEMM_CFG);
@@ -1122,10 +1129,15 @@ size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co) {
   size_t b = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
   if (N >= 1 && conv_wg_fits(N, H, W, Ci, Co, nullptr, nullptr, nullptr)) {
     // the large-tile kernel's split partials
-    const size_t w = conv_wg_ws_bytes(N, H, W, Ci, Co);
+    const size_t w = conv_wg_ws_bytes(N, H, W, Ci, Co, b);
     if (w > b) b = w;
   }
   return b;
+}
+
+size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co) {
+  if (Ci % 64 || Co % 64 || N < 1) return 0;
+  return conv_plan(3, N, H, W, Ci, Co).ws_bytes;
 }
 
 static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void *A, const void *B, void *out,
@@ -1139,7 +1151,7 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
   if (pass == 3) {
     // the template's partials are the least that a call has to bring; the large-tile kernel
     // takes as many splits as fit into what it is given
-    const size_t least = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
+    const size_t least = conv_wgrad_ws_least(N, H, W, Ci, Co);
     if (least > 0 && (ws == nullptr || ws_bytes < least || (uintptr_t)ws % 16)) {
       set_error("conv weight gradient needs %zu bytes of 16-byte aligned workspace, got %zu", least, ws_bytes);
       return IMBD_EWORKSPACE;
@@ -1150,7 +1162,8 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
     }
   }
   if (pass == 3 && conv_wg_fits(N, H, W, Ci, Co, A, B, out))
-    return run_conv_wg(N, H, W, Ci, Co, A, B, reinterpret_cast<float *>(out), ws, ws_bytes, s);
+    return run_conv_wg(N, H, W, Ci, Co, A, B, reinterpret_cast<float *>(out), ws, ws_bytes,
+                       conv_wgrad_ws_least(N, H, W, Ci, Co), s);
   const ConvPlan pl = conv_plan(pass, N, H, W, Ci, Co);
   if ((int64_t)N * (H + 2) * (W + 2) * (Ci > Co ? Ci : Co) >= ((int64_t)1 << 31)) {
     set_error("conv tile too large for 32-bit element offsets");
