@@ -445,14 +445,16 @@ struct SkSoftmaxArgs {
 // Top layer, one workgroup per sample (four consecutive classes per thread, C <= 1024): the
 // logit is the splits' partials added in split order plus the bias (the same arithmetic as
 // the reduce), stored; then softmax cross-entropy over the row: maximum, sum of
-// exp(z - max) (each thread's classes in order, the wave in shuffle order, the waves' values
-// in wave order), per-sample loss lse - z[label] and the gradient
+// exp(z - max), per-sample loss lse - z[label] and the gradient
 // inv_batch * (softmax - onehot); NaN loss and gradient row for a label outside [0, C).
+// The order of that sum is part of the result's bits and does not depend on the layout: 64
+// consecutive classes as a butterfly (partners 32, 16, .. 1 classes apart), the groups of 64
+// in order, as one class per lane of a wave gives it.
 // A row is a chain of loads and two exchanges, so what counts is how many rows a CU holds
 // at once: a quarter of the threads that one class each would take (2048 rows of 1000 classes
 // on four splits: 20.5 -> 12.2 us; 256 rows on eight: 6.5 -> 6.1).
 __global__ void __launch_bounds__(256) skinny_softmax_rows(SkSoftmaxArgs g) {
-  __shared__ float red[2][4];
+  __shared__ float red[4], sums[16];
   const int row = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int nw = (int)blockDim.x >> 6, c = 4 * t, cnt = min(4, g.C - c);  // cnt <= 0: no class here
   const int lab = g.labels[row];
@@ -489,20 +491,24 @@ __global__ void __launch_bounds__(256) skinny_softmax_rows(SkSoftmaxArgs g) {
   float mx = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  if (lane == 0) red[0][w] = mx;
+  if (lane == 0) red[w] = mx;
   __syncthreads();
-  mx = red[0][0];
-  for (int k = 1; k < nw; ++k) mx = fmaxf(mx, red[0][k]);
+  mx = red[0];
+  for (int k = 1; k < nw; ++k) mx = fmaxf(mx, red[k]);
   f32x4 e;
 #pragma unroll
   for (int i = 0; i < 4; ++i) e[i] = i < cnt ? expf(z[i] - mx) : 0.0f;
-  float s = ((e[0] + e[1]) + e[2]) + e[3];
+  // 16 threads hold 64 classes: partners 32 to 4 classes apart are 8 to 1 threads apart, 2 and
+  // 1 the thread's own
+  f32x4 v = e;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (lane == 0) red[1][w] = s;
+  for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] += __shfl_xor(v[i], o, 64);
+  if ((t & 15) == 0) sums[t >> 4] = (v[0] + v[2]) + (v[1] + v[3]);
   __syncthreads();
-  s = red[1][0];
-  for (int k = 1; k < nw; ++k) s += red[1][k];
+  float s = sums[0];
+  for (int k = 1; k < (g.C + 63) >> 6; ++k) s += sums[k];
   const bool ok = lab >= 0 && lab < g.C;
   const int at = (ok ? lab : 0) - c;  // the thread that holds the label's class writes the loss
 #pragma unroll

@@ -558,3 +558,40 @@ def test_top_layer_softmax_class_counts(imbd, dev, B, C):
     assert abs(loss.item() - rows.mean()) < 1e-5 * max(1.0, abs(rows.mean()))
     got = host(imbd.ws_view(net, ws, imbd.IMBD_WS_DY, 1))
     assert np.abs(got - dz / B).max() <= (2.0 ** -8 + 1e-5) * max(np.abs(dz / B).max(), 1e-30)
+
+
+@pytest.mark.parametrize("B,C", [(40, 7), (40, 64), (40, 130), (40, 1000), (40, 1024), (300, 264), (300, 1000)])
+def test_top_layer_softmax_sum_order(imbd, dev, B, C):
+    """The order in which the top layer's pass adds exp(z - max), which the outputs' bits depend on:
+    64 consecutive classes as a butterfly (partners 32, 16, .. 1 classes apart), the groups of 64 in
+    order. One logit of a row is 0 (and its label), a few are -17, the others vanish: each
+    e^-17 = 4.1e-8 alone is less than half a unit in the last place of 1 and is lost, two that
+    meet first are not, so log(sum), the row's loss, tells the order."""
+    import torch
+    rng = np.random.default_rng(1000 * B + C)
+    K = 1024
+    z = np.full((B, C), -200.0, np.float32)
+    lab = rng.integers(0, C, B).astype(np.int32)
+    for b in range(B):
+        z[b, rng.integers(0, C, min(C, rng.integers(1, 14)))] = -17.0
+    z[np.arange(B), lab] = 0.0
+    w = np.zeros((C, K), np.float32)
+    w[:, :B] = z.T  # sample b is the unit vector b: its logits are column b, exactly
+    w32 = dev_f32(w, dev)
+    layers = [{"w": w32, "w_lp": w32.to(torch.bfloat16), "b": torch.zeros(C, device=dev)}]
+    net = imbd.MLP((K, C), B, "bf16")
+    ws = torch.zeros(imbd.mlp_workspace_bytes(net), dtype=torch.uint8, device=dev)
+    loss = torch.zeros(1, device=dev)
+    imbd.mlp_fwd(net, layers, torch.eye(B, K, device=dev).to(torch.bfloat16), torch.from_numpy(lab).to(dev), ws, loss)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(imbd.ws_view(net, ws, imbd.IMBD_WS_LOGITS)), z)
+    e = np.zeros((B, (C + 63) // 64, 64), np.float32)
+    e.reshape(B, -1)[:, :C] = np.exp(z)
+    at = np.arange(64)
+    for o in (32, 16, 8, 4, 2, 1):
+        e = e + e[:, :, at ^ o]
+    s = e[:, 0, 0]
+    for k in range(1, e.shape[1]):
+        s = s + e[:, k, 0]
+    # a quarter of the step between neighbouring sums; log of a value this close to 1 is good to 1e-6 of itself
+    assert np.abs(host(imbd.ws_view(net, ws, imbd.IMBD_WS_ROWLOSS)) - np.log(s.astype(np.float64))).max() < 2.0 ** -25
