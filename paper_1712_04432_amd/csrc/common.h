@@ -187,8 +187,10 @@ bool dw_sgd_fits(const GemmProblem &p);
 // write the reduce's partials or read its output.
 int run_dw_sgd(const GemmProblem &p, hipStream_t s, const ReduceTail *tail = nullptr);
 // The weight gradient on large tiles (bf16; the SGD update past 256 samples or the fp32
-// store of alpha * Delta_W at any batch, in each tile's epilogue, the bias gradient by the
-// first column tiles): whether it takes the problem, and the launch.
+// store of alpha * Delta_W at any batch, in each tile's epilogue, the bias gradient by
+// workgroups beside the tiles' or by the first column tile's; past 512 samples, where there
+// is no room for the former, on the column-sum kernel): whether it takes the problem, and the
+// launch.
 bool dw_wide_fits(const GemmProblem &p);
 // tail (kind 2, fused update only): a wide-batch product's split-K reduce that every
 // workgroup takes a share of after its tile; the launch must not write the reduce's

@@ -3,7 +3,9 @@
 //   Delta_W[o][i] = sum_b Delta_Y[b][o] X[b][i]      (Sec. 1, K = the batch)
 //   w[o][i] -= lr * alpha * Delta_W[o][i];  w16[o][i] = bf16(w[o][i])   (Eq. (1))
 // (or, for the unfused and local backward passes, alpha * Delta_W stored as fp32). The
-// bias gradient (column sums of Delta_Y) comes from the workgroups of the first column tile.
+// bias gradient (column sums of Delta_Y) comes from workgroups of its own in the launch or,
+// where there is no room for them, from the workgroups of the first column tile up to 512
+// samples and from the column-sum kernel past them.
 //
 // At these batch sizes the product (2 x batch flops per weight) outweighs the update's
 // 10 bytes per weight, so the kernel takes the large-tile layout of the conv tile's
@@ -32,11 +34,12 @@
 namespace imbd {
 namespace {
 
-// the kernel: one tile per workgroup
+// the kernel: one tile (or the bias sums of some columns) per workgroup
 template <bool SGD, int OH, bool DUAL>
 __global__ void __launch_bounds__(512, DUAL ? 2 : 1) dw_wide_kernel(DlArgs a) {
   __shared__ __attribute__((aligned(1024))) char smem[dl_lds_bytes<OH, DUAL>()];
-  dw_wide_body<SGD, OH, DUAL>(a, smem, (int)blockIdx.x, (int)gridDim.x);
+  if ((int)blockIdx.x < a.db_blocks) dl_bias_block<OH>(a, smem, (int)blockIdx.x);
+  else dw_wide_body<SGD, OH, DUAL>(a, smem, (int)blockIdx.x - a.db_blocks, (int)gridDim.x - a.db_blocks);
   if constexpr (SGD) {
     // the reduce this launch carries (another layer's Delta_X partials into its Delta_Y):
     // eight outputs of one sample per item, a share of them per workgroup after its tile
@@ -112,12 +115,12 @@ void dw_wide_prepare(const GemmProblem &p, int extra_blocks, DlArgs *out, int *o
   const int dual_opt = opt(IMBD_OPT_DW_WIDE_DUAL);
   const bool dual = extra_blocks == 0 && (dual_opt == 1 || (dual_opt == -1 && t128 > 256));
   // (4-byte pieces: 128-row tiles, whose loads in flight fit the memory counter)
-  // (one column tile cannot hold the bias sums of 256-row tiles, which take two)
-  const bool half = dual || p.b_dw4 || (p.db_mode != 0 && ti == 1) || ((t128 + 255) / 256) * 128 * 11 < ((t256 + 255) / 256) * 256 * 10;
+  const bool half = dual || p.b_dw4 || ((t128 + 255) / 256) * 128 * 11 < ((t256 + 255) / 256) * 256 * 10;
   const int oh = half ? 128 : 256;
   a.tiles_o = (p.N + oh - 1) / oh;
   a.tiles_i = (p.M + 127) / 128;
   a.db_mode = p.db_mode;
+  a.db_blocks = 0;
   a.db_alpha = p.db_alpha;
   a.bias_lr = p.bias_lr;
   a.db_out = p.db_out;
@@ -136,6 +139,18 @@ int run_dw_wide(const GemmProblem &p, hipStream_t s, const ReduceTail *tail) {
   bool dual;
   dw_wide_prepare(p, 0, &a, &oh, &dual, &grid);
   const bool sgd = p.epi.mode == EPI_SGD, half = oh == 128;
+  // The bias sums: workgroups of their own, dispatched first, where the tiles take several
+  // rounds anyhow (two workgroups per CU) or leave CUs free; they do not start a second round.
+  // Each way keeps its order of the sums.
+  bool db_apart = false;
+  if (p.db_mode != 0) {
+    const bool cols = p.K > 512;
+    const int nb = ((p.N + (cols ? 128 : oh) - 1) / (cols ? 128 : oh) + 7) / 8 * 8;
+    if ((dual || grid + nb <= 256) && (!cols || bias_cols64_ok(p.N, p.B, p.ldb))) a.db_blocks = nb;
+    else db_apart = cols;
+    if (db_apart) a.db_mode = 0;
+    grid += a.db_blocks;
+  }
   if (tail && tail->kind == 2 && sgd) {
     a.tail = tail->lean;
     a.tail_items = tail->items;
@@ -156,7 +171,10 @@ int run_dw_wide(const GemmProblem &p, hipStream_t s, const ReduceTail *tail) {
       else hipLaunchKernelGGL((dw_wide_kernel<false, 256, false>), dim3(grid), dim3(512), 0, s, a);
     }
   }
-  return check_launch("dw_wide");
+  const int rc = check_launch("dw_wide");
+  if (rc != IMBD_OK || !db_apart) return rc;
+  return run_bias_grad(IMBD_BF16, p.N, p.K, p.B, p.ldb, p.db_alpha, p.db_mode == 1 ? p.db_out : nullptr,
+                       p.db_mode == 2 ? p.bias : nullptr, p.bias_lr, s, p.layer);
 }
 
 }  // namespace imbd

@@ -6,6 +6,7 @@
 //   w[o][i] -= lr * alpha * Delta_W[o][i];  w16[o][i] = bf16(w[o][i])   (Eq. (1))
 #pragma once
 
+#include "bias_cols.h"
 #include "cdna4.h"
 
 namespace imbd {
@@ -29,11 +30,13 @@ struct DlArgs {
   uint32_t w_bytes, w16_bytes;
   float lr, alpha;
   int tiles_o, tiles_i;
-  // bias gradient, db[o] = db_alpha * sum_b Delta_Y[b][o], by the workgroups of the first
-  // column tiles (db_mode 0: none, 1: store db_out, 2: bias -= bias_lr * db)
+  // bias gradient, db[o] = db_alpha * sum_b Delta_Y[b][o] (db_mode 0: none, 1: store db_out,
+  // 2: bias -= bias_lr * db), by the workgroups of the first column tile or, with db_blocks
+  // > 0, by that many workgroups in front of the tiles' (a multiple of 8)
   int db_mode;
   float db_alpha, bias_lr;
   float *db_out, *bias;
+  int db_blocks;
   // Delta_Y's rows only 4-byte aligned (pitch and base): loaded in 4-byte pieces
   int dy_dw4;
   // a wide-batch product's split-K reduce (mask, bf16 output) carried by the fused-update
@@ -56,6 +59,54 @@ constexpr int dl_lds_bytes() {
   return (DUAL ? 5 : DL_ND) * (DUAL ? 32 : 64) * 2 * OH + (DUAL ? 5 : DL_NX) * (DUAL ? 32 : 64) * 256;
 }
 
+// The bias gradient of rows o0 .. o0 + OH - 1 up to 512 samples, by 512 threads: thread t sums
+// column o0 + t%OH over the samples of its part (t/OH of 512/OH parts) in ascending order, the
+// parts are added in order. part: 512 floats of LDS.
+template <int OH>
+__device__ __forceinline__ void dl_bias_parts(const DlArgs &a, float *part, int o0) {
+  constexpr int NP = 512 / OH;
+  const int tid = threadIdx.x;
+  const int col = tid % OH, pi = tid / OH, o = o0 + col;
+  const int kh = (a.K + NP - 1) / NP, b0 = min(a.K, pi * kh), b1 = min(a.K, b0 + kh);
+  float sum = 0.f;
+  if (o < a.N) {
+    const uint16_t *p = a.DY + o;
+    int b = b0;
+    for (; b + 8 <= b1; b += 8) {
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = bf16_to_f32(p[(int64_t)(b + q) * a.lddy]);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sum += v[q];
+    }
+    for (; b < b1; ++b) sum += bf16_to_f32(p[(int64_t)b * a.lddy]);
+  }
+  part[tid] = sum;
+  __syncthreads();
+  if (tid < OH && o < a.N) {
+    float t = part[tid];
+#pragma unroll
+    for (int q = 1; q < NP; ++q) t += part[tid + q * OH];
+    const float db = a.db_alpha * t;
+    if (a.db_mode == 1) a.db_out[o] = db;
+    else a.bias[o] -= a.bias_lr * db;
+  }
+}
+
+// The bias gradient by a workgroup of its own (b of a.db_blocks) in front of the tiles: OH
+// columns up to 512 samples, past them 128 columns in the order of the column-sum kernel.
+template <int OH>
+__device__ __forceinline__ void dl_bias_block(const DlArgs &a, char *smem, int b) {
+  if (a.K <= 512) {
+    if (b * OH < a.N) dl_bias_parts<OH>(a, reinterpret_cast<float *>(smem), b * OH);
+    return;
+  }
+  const int half = (int)threadIdx.x >> 8;
+  bias_cols64(a.N, a.K, a.DY, a.lddy, a.db_alpha, a.db_mode == 1 ? a.db_out : nullptr,
+              a.db_mode == 2 ? a.bias : nullptr, a.bias_lr, (2 * b + half) * 64, (int)threadIdx.x & 255,
+              reinterpret_cast<float(*)[BIAS_PITCH]>(smem + half * 32 * BIAS_PITCH * 4));
+}
+
 // One workgroup's tile: bid is its index in the launch order of the G (a multiple of 8)
 // workgroups that share the work, smem its LDS (dl_lds_bytes<OH, DUAL>() bytes).
 template <bool SGD, int OH, bool DUAL>
@@ -72,7 +123,7 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
   static_assert(DRING + XRING == dl_lds_bytes<OH, DUAL>(), "LDS size");
   static_assert(!DUAL || OH == 128, "two workgroups per CU: 128-row tiles");
   static_assert(DRING + XRING <= (DUAL ? 80 : 160) * 1024, "LDS");
-  static_assert(OH * DL_PITCH * 4 <= DRING + XRING, "staging");
+  static_assert(OH * DL_PITCH * 4 + 512 * 4 <= DRING + XRING, "staging and bias sums");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -245,29 +296,11 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
 #pragma unroll
       for (int j = 0; j < 4; ++j) xd[j] = tr8(xs + fx[j] + (uint32_t)(s * 4096));
     };
-    // The bias gradient, the row sums of the Delta_Y fragments: in the first column tile (the
-    // first two of 256-row tiles) each wave multiplies two of its row blocks by ones too
-    // (every column of the product is the sum): an eighth (a sixteenth) more MFMAs in one
-    // (two) of a row's many tiles, and eight registers. (Summed from memory by the tile's
-    // threads afterwards, up to 512 samples, or by a launch of its own past them:
-    // 9216-4096-4096-1000 at 2048 samples spent 3 x 9.5 us on those launches.)
-    const bool dodb = it < FM / 4 && a.db_mode != 0;
-    const int ib = (FM == 8 ? 2 * it : 0) + wn;  // the wave's pair of row blocks
-    f32x4 accb[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
     auto mma = [&](const bf16x8 (&df)[FM], const bf16x8 (&xf)[4]) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[i], xf[j], acc[i][j], 0, 0, 0);
-      if (dodb) {
-#pragma unroll
-        for (int q = 0; q < FM / 2; ++q)
-          if (q == ib) {
-            accb[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[2 * q], ones, accb[0], 0, 0, 0);
-            accb[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df[2 * q + 1], ones, accb[1], 0, 0, 0);
-          }
-      }
     };
     uint32_t ds = ldsd, xs = ldsx;
     lds_barrier();  // B_0
@@ -285,7 +318,6 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
           __builtin_amdgcn_sched_barrier(0);
-          if (dodb && (i >> 1) == ib) accb[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dv[0][i], ones, accb[i & 1], 0, 0, 0);
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dv[0][i], xv[0][j], acc[i][j], 0, 0, 0);
@@ -316,19 +348,6 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
       }
     }
     if constexpr (EARLY) load_masters();
-    if (dodb && fi == 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int o = o0 + 16 * (FM * wm + 2 * ib + i) + 4 * kg + e;
-          if (o < a.N) {
-            const float db = a.db_alpha * accb[i][e];
-            if (a.db_mode == 1) a.db_out[o] = db;
-            else a.bias[o] -= a.bias_lr * db;
-          }
-        }
-    }
     // ---- stage the tile as [o][i] fp32
     float *stg = reinterpret_cast<float *>(smem);
 #pragma unroll
@@ -338,6 +357,10 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           stg[(16 * (FM * wm + i) + 4 * kg + e) * DL_PITCH + 16 * (4 * wn + j) + fi] = acc[i][j][e];
+  }
+  if (it == 0 && a.db_mode != 0 && a.db_blocks == 0) {
+    __syncthreads();  // (the staged tile leaves LDS free past it)
+    dl_bias_parts<OH>(a, reinterpret_cast<float *>(smem + OH * DL_PITCH * 4), o0);
   }
   // ---- the update: thread (sub, ch) takes rows o0 + US*u + sub (u < UR), columns
   // i0 + 4ch .. +3, with all its rows' masters in flight at once. One workgroup per CU: the

@@ -595,3 +595,39 @@ def test_top_layer_softmax_sum_order(imbd, dev, B, C):
         s = s + e[:, k, 0]
     # a quarter of the step between neighbouring sums; log of a value this close to 1 is good to 1e-6 of itself
     assert np.abs(host(imbd.ws_view(net, ws, imbd.IMBD_WS_ROWLOSS)) - np.log(s.astype(np.float64))).max() < 2.0 ** -25
+
+
+@pytest.mark.parametrize("b,dout,din", [
+    # the first column tile's own sums; workgroups in front of the tiles, in a launch of one
+    # round and (more than 256 tiles) of several; the last columns ragged
+    (300, 2048, 2048), (300, 136, 512), (512, 1000, 4608), (257, 4104, 2048),
+    # past 512 samples: workgroups in front of the tiles; no room for them (a column-sum launch)
+    (513, 264, 640), (1100, 1000, 4608), (700, 2048, 2048), (2048, 1000, 2048)])
+def test_bias_gradient_sum_order(imbd, dev, b, dout, din):
+    """The order in which the large-tile weight gradient's launch adds up the bias gradient, which
+    the outputs' bits depend on: up to 512 samples four parts in ascending order each, added in
+    order; past them 32 interleaved row phases, added in order."""
+    import torch
+    rng = np.random.default_rng(b + dout)
+    dy = torch.from_numpy(rng.standard_normal((b, dout)).astype(np.float32)).to(dev).to(torch.bfloat16)
+    x = torch.zeros((b, din), dtype=torch.bfloat16, device=dev)
+    w = torch.zeros((dout, din), dtype=torch.bfloat16, device=dev)
+    dw = torch.zeros((dout, din), device=dev)
+    db = torch.zeros(dout, device=dev)
+    ws = torch.zeros(max(16, imbd.mlp_local_workspace_bytes(1, imbd.dtype_code(w.dtype), dout, din, b)),
+                     dtype=torch.uint8, device=dev)
+    imbd.mlp_local_bwd(w, dy, x, dw, 1, 1, db_part=db, ws=ws)
+    torch.cuda.synchronize()
+    v = dy.float().cpu().numpy()
+    if b <= 512:
+        kh = (b + 3) // 4
+        parts = [v[p * kh:(p + 1) * kh] for p in range(4)]
+    else:
+        parts = [v[p::32] for p in range(32)]
+    total = np.zeros(dout, np.float32)
+    for p in parts:
+        s = np.zeros(dout, np.float32)
+        for row in p:
+            s = s + row
+        total = total + s
+    assert np.array_equal(db.cpu().numpy(), np.float32(1.0 / b) * total)
