@@ -856,9 +856,17 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
   auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
   // byte offsets of both operands within one buffer descriptor; image rows and columns
   // within the range of the kernel's short divisions
+  const int64_t P = (int64_t)N * (H + 2) * (W + 2);
+  // Tensors of 2^31 elements and more are left to the tiled template, which refuses them; at
+  // 256 output channels they are taken while the activations, with the rows that the last
+  // tile may touch, stay within the descriptor. So a workgroup's share is at most 2^13
+  // position blocks (M * Cn < 2^31 over 256 workgroups of 128 channels; M < 2^24 at 256
+  // channels), and the tile bounds' products fit 32 bits.
+  if (P * (Ci > Co ? Ci : Co) >= ((int64_t)1 << 31) &&
+      !(Cn == 256 && (P + 2 * (W + 2) + 130) * Ck * 2 < ((int64_t)1 << 31)))
+    return false;
   return (pass == 1 || pass == 2) && N >= 1 && H >= 1 && W >= 1 && Cn >= 64 && Cn % 64 == 0 && Ck >= 64 &&
-         Ck % 64 == 0 && al(act) && al(w) && al(out) && H < 32768 && W < 32768 &&
-         (int64_t)N * (H + 2) * (W + 2) * Ck * 2 < ((int64_t)1 << 31) &&
+         Ck % 64 == 0 && al(act) && al(w) && al(out) && H < 32768 && W < 32768 && P * Ck * 2 < ((int64_t)1 << 31) &&
          (int64_t)9 * Ci * Co * 2 < ((int64_t)1 << 31);
 }
 

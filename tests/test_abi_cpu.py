@@ -234,3 +234,16 @@ def test_static_scratch_refuses_oversized_network_on_the_host(lib):
     assert b"static scratch" in lib.imbd_last_error()
     bad = m.MLP((8, 0, 2), 4, "bf16")
     assert lib.mlp_train_step_static(bad.desc, layers, p, p, 0.01, p, None) == m.IMBD_EINVAL
+
+
+@pytest.mark.parametrize("N,H,W,narrow,wide", [(1024, 56, 56, 64, 16448), (700, 56, 56, 64, 1024), (8, 1, 500000, 64, 1024)])
+def test_conv_refuses_tensors_past_32_bit_elements(lib, N, H, W, narrow, wide):
+    """A conv tile whose output has 2^31 elements or more is refused (256 output channels excepted),
+    also where its input is small enough for the large-tile kernel: there one workgroup's share
+    of the first size, 200704 position blocks in 12544 tiles, overflows the tile bounds'
+    products."""
+    import paper_1712_04432_amd as m
+    p = ctypes.c_void_p(1 << 20)
+    for dtype in (0, 1):
+        assert lib.conv3x3_tile_fwd(N, H, W, narrow, wide, p, p, p, dtype, None) == m.IMBD_EUNSUPPORTED
+        assert lib.conv3x3_tile_dgrad(N, H, W, wide, narrow, p, p, p, dtype, None) == m.IMBD_EUNSUPPORTED
