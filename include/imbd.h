@@ -255,7 +255,7 @@ enum imbd_option {
     IMBD_OPT_DW_STREAM = 6,     /* 0: past 256 samples the persistent update kernel reloads its
                                    Delta_Y block per 256 samples instead of streaming it */
     IMBD_OPT_DW_GENERIC = 7,    /* 1: the fused update on the tiled template */
-    IMBD_OPT_GEMM_CFG = 8,      /* tile configuration of the tiled template, -1 = planned (-1..3) */
+    IMBD_OPT_GEMM_CFG = 8,      /* tile configuration of the tiled template, -1 = planned (-1..4) */
     IMBD_OPT_GEMM_SPLITS = 9,   /* K split of the tiled template, 0 = planned */
     IMBD_OPT_CONV_NT = 10,      /* 0: the conv tile on the tiled template; 1: on the large-tile
                                    kernels, tile height planned (default); 2 / 3: with tiles of

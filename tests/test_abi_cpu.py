@@ -194,6 +194,11 @@ def test_options_set_get_and_validation(lib, monkeypatch):
     assert m.get_option(m.IMBD_OPT_WIDE_SPLITS) == old and m.get_option(m.IMBD_OPT_DW_STREAM) == 1
     assert lib.imbd_set_option(m.IMBD_OPT_SKINNY_OFF, 2) == m.IMBD_EINVAL
     assert lib.imbd_set_option(m.IMBD_OPT_GEMM_CFG, -2) == m.IMBD_EINVAL
+    # every tile configuration of the template (128 x 128 to 32 x 32) can be forced
+    for c in range(5):
+        with m.options(gemm_cfg=c):
+            assert m.get_option(m.IMBD_OPT_GEMM_CFG) == c
+    assert lib.imbd_set_option(m.IMBD_OPT_GEMM_CFG, 5) == m.IMBD_EINVAL
     assert lib.imbd_set_option(m.IMBD_OPT_COUNT, 0) == m.IMBD_EINVAL
     assert lib.imbd_set_option(-1, 0) == m.IMBD_EINVAL
     assert lib.imbd_get_option(0, None) == m.IMBD_EINVAL
