@@ -60,9 +60,10 @@ struct KMask {
   int wp = 1, hp = 1, w = 1, h = 1;
 };
 
-// The loaders' fast path (G = false) loads whole vectors from clamped addresses and keeps a
-// bit per vector that says whether it counts; the others are zeroed when they are stored to
-// LDS. (Zeroed at the load, the compiler moved the selects of the newest loads in front of
+// The loaders' fast path (G = false) loads whole vectors from clamped addresses; those that
+// don't count are zeroed when they are stored to LDS, in a branch that only a K tile at an
+// edge of the operand takes (which vectors they are is worked out again there: kept from the
+// load, they cost registers that the 128 x 128 tiles don't have). (Zeroed at the load, the compiler moved the selects of the newest loads in front of
 // the older stage's stores, so that every second K tile waited for its own loads. The fp32
 // 9216-4096-4096-1000 step at 256 samples: 800 -> 758 us, with its short weight gradient
 // whole. With the vector loads at any address in the place of element loads, the bf16
@@ -74,15 +75,11 @@ struct KcLoader {
   static constexpr int VEC = Elem<T>::VEC;
   static constexpr int CH = R * 8;
   static constexpr int PER = (CH + NT - 1) / NT;
-  static constexpr uint32_t ALL = (1u << PER) - 1;
   u32x4 v[PER];
-  uint32_t ok;
 
   // G: guarded (masked element by element); !G: whole chunks (kend is a multiple of VEC)
-  template <bool G, bool KM = false>
-  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int rows, int k0,
-                                       int kend, int tid, KMask = KMask{}) {
-    ok = ALL;
+  template <bool G>
+  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int rows, int k0, int kend, int tid) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * NT;
@@ -96,16 +93,19 @@ struct KcLoader {
         } else {
           const T *p = base + (int64_t)min(grow, rows - 1) * ld + min(kk, kend - VEC);
           v[i] = *reinterpret_cast<const u32x4_any *>(p);
-          if (!(grow < rows && kk < kend)) ok &= ~(1u << i);
         }
       }
     }
   }
-  __device__ __forceinline__ void store(char *lds, int tid) {
-    if (ok != ALL) {
+  // row0 .. kend as they were loaded with (fast path)
+  template <bool G>
+  __device__ __forceinline__ void store(char *lds, int row0, int rows, int k0, int kend, int tid) {
+    if (!G && (row0 + R > rows || k0 + 8 * VEC > kend)) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (!(ok >> i & 1u)) v[i] = u32x4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < PER; ++i) {
+        const int c = tid + i * NT;
+        if (row0 + (c >> 3) >= rows || k0 + (c & 7) * VEC >= kend) v[i] = u32x4{0u, 0u, 0u, 0u};
+      }
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -127,62 +127,61 @@ struct TrLoader {
   static constexpr int VEC = Elem<T>::VEC;
   static constexpr int NB = 8 * (R / VEC);
   static constexpr int PER = (NB + NT - 1) / NT;
-  static constexpr uint32_t ALL = (uint32_t)((1ull << (PER * VEC)) - 1);
   u32x4 v[PER][VEC];
-  uint32_t ok;
 
-  // KM: k indexes positions of a zero-padded (hp x wp) image grid; rows whose position
-  // falls outside the inner (h x w) image read as zero.
-  template <bool G, bool KM = false>
-  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int rows, int k0,
-                                       int kend, int tid, KMask km = KMask{}) {
-    ok = ALL;
+  template <bool G>
+  __device__ __forceinline__ void load(const T *base, int64_t ld, int row0, int rows, int k0, int kend, int tid) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int blk = tid + i * NT;
       if (NB % NT == 0 || blk < NB) {
         const int kb = blk & 7, rb = blk >> 3;
         const int col = row0 + rb * VEC;
-        int wpos = 0, hpos = 0;
-        if constexpr (KM) {
-          const int kf = k0 + kb * VEC;
-          const int q = kf / km.wp;
-          wpos = kf - q * km.wp;
-          hpos = q % km.hp;
-        }
+        const T *p = base + (int64_t)min(k0 + kb * VEC, kend - 1) * ld + (col < rows ? col : 0);
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
           const int k = k0 + kb * VEC + j;
-          bool inside = true;
-          if constexpr (KM) {
-            int w = wpos + j, h = hpos;
-            while (w >= km.wp) {  // wraps into the next grid rows (more than one in narrow grids)
-              w -= km.wp;
-              h = (h + 1 == km.hp) ? 0 : h + 1;
-            }
-            inside = (w < km.w) && (h < km.h);
-          }
           if constexpr (G) {
-            const int valid = (k < kend && inside) ? (rows - col) : 0;
+            const int valid = k < kend ? (rows - col) : 0;
             v[i][j] = load16<T>(base + (int64_t)k * ld + col, valid);
           } else {
             // (rows >= VEC. A last chunk that goes past `rows` reads on into the next k-row,
             // which the caller says exists; it feeds only outputs that are not stored.)
-            const T *p = base + (int64_t)min(k, kend - 1) * ld + (col < rows ? col : 0);
             v[i][j] = *reinterpret_cast<const u32x4_any *>(p);
-            if (!(inside && k < kend && col < rows)) ok &= ~(1u << (i * VEC + j));
+            p += k + 1 < kend ? ld : 0;
           }
         }
       }
     }
   }
-  __device__ __forceinline__ void store(char *lds, int tid) {
-    if (ok != ALL) {
+  // row0 .. kend as they were loaded with (fast path). KM: k indexes positions of a zero-padded
+  // (hp x wp) image grid; rows whose position falls outside the inner (h x w) image are zero.
+  template <bool G, bool KM = false>
+  __device__ __forceinline__ void store(char *lds, int row0, int rows, int k0, int kend, int tid, KMask km = KMask{}) {
+    if constexpr (KM) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
+      for (int i = 0; i < PER; ++i) {
+        const int kf = k0 + ((tid + i * NT) & 7) * VEC, q = kf / km.wp;
+        int w = kf - q * km.wp, h = q % km.hp;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+          if (w >= km.w || h >= km.h) v[i][j] = u32x4{0u, 0u, 0u, 0u};
+          if (++w == km.wp) {  // on into the next grid row
+            w = 0;
+            h = (h + 1 == km.hp) ? 0 : h + 1;
+          }
+        }
+      }
+    }
+    if (!G && (row0 + R > rows || k0 + 8 * VEC > kend)) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int blk = tid + i * NT;
+        const int k = k0 + (blk & 7) * VEC, left = row0 + (blk >> 3) * VEC < rows ? kend - k : 0;
 #pragma unroll
         for (int j = 0; j < VEC; ++j)
-          if (!(ok >> (i * VEC + j) & 1u)) v[i][j] = u32x4{0u, 0u, 0u, 0u};
+          if (j >= left) v[i][j] = u32x4{0u, 0u, 0u, 0u};
+      }
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -439,8 +438,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   const T *Bp = reinterpret_cast<const T *>(g.B);
   // Two register stages: while tile kt is multiplied out of LDS, the global loads of
   // tiles kt+1 and kt+2 are both in flight. The weight-gradient product (short K, its
-  // registers taken by the prefetched master tile) keeps one stage.
-  constexpr int NSTAGE = PREFETCH_W ? 1 : 2;
+  // registers taken by the prefetched master tile) keeps one stage, and so does the conv
+  // weight gradient (its position masks; two stages spilled registers).
+  constexpr int NSTAGE = PREFETCH_W || CONV == 3 ? 1 : 2;
   typename LoaderSel<T, BM, NT, A_KC>::type la[NSTAGE];
   typename LoaderSel<T, BN, NT, B_KC>::type lb[NSTAGE];
 
@@ -455,9 +455,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   // last iterations re-load the last tile instead of skipping the load, and an odd tile count
   // is padded with one all-zero tile). Operands at any element alignment take it; where a
   // chunk can be cut (K ends off a multiple of VEC, a transposed operand whose width is
-  // none), the split's last K tile comes after them with loads masked element by element.
-  const bool fast = nk > 0 && (A_KC || g.M >= VEC) && (B_KC || g.N >= VEC);
-  const bool ragged = ((A_KC || B_KC) && kend % VEC != 0) || (!A_KC && g.M % VEC != 0) || (!B_KC && g.N % VEC != 0);
+  // none), the split's last K tile comes after them with loads masked element by element. (A
+  // conv tile's channel counts are multiples of 64: no chunk of it is cut.)
+  const bool fast = nk > 0 && (CONV != 0 || ((A_KC || g.M >= VEC) && (B_KC || g.N >= VEC)));
+  const bool ragged = CONV == 0 && (((A_KC || B_KC) && kend % VEC != 0) || (!A_KC && g.M % VEC != 0) ||
+                                    (!B_KC && g.N % VEC != 0));
   const int nkf = fast ? (ragged ? nk - 1 : nk) : 0;  // K tiles of the fast path
   const int kend_f = ragged ? kbeg + nkf * BK : kend;
   const int nk_fast = (nkf + NSTAGE - 1) / NSTAGE * NSTAGE;
@@ -564,10 +566,26 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
       L.template load<G>(Bp + (int64_t)((2 - r) * Wp + 2 - sx) * g.cCo, g.ldb, n0, g.N, o0, g.cCo, tid_b);
     } else if constexpr (CONV == 3) {
       // interior of dy_pad, rows outside the inner image masked to zero
-      L.template load<G, true>(Bp, g.ldb, n0, g.N, kg, kend_g, tid_b, km);
+      L.template load<G>(Bp, g.ldb, n0, g.N, kg, kend_g, tid_b);
     } else {
       L.template load<G>(Bp, g.ldb, n0, g.N, kg, kend_g, tid_b);
     }
+  };
+  // The other half of a load: K tile kt's vectors into its LDS buffer. (A conv tile's channels
+  // fill whole tiles; its k chunks count wholly or, past the K range, not at all.)
+  auto storeA = [&](auto &L, int kt, auto gtag) {
+    constexpr bool G = decltype(gtag)::value;
+    const int kg = kbeg + kt * BK;
+    if constexpr (CONV == 1 || CONV == 2) L.template store<G>(buf(kt), 0, BM, 0, kg < kend_f ? BK : 0, tid);
+    else if constexpr (CONV == 3) L.template store<G>(buf(kt), 0, BM, kg, kend_f, tid);
+    else L.template store<G>(buf(kt), m0, g.M, kg, kend_f, tid);
+  };
+  auto storeB = [&](auto &L, int kt, auto gtag) {
+    constexpr bool G = decltype(gtag)::value;
+    const int kg = kbeg + kt * BK;
+    if constexpr (CONV == 1 || CONV == 2) L.template store<G>(buf(kt) + STAGE_A, n0, g.N, 0, kg < kend_f ? BK : 0, tid_b);
+    else if constexpr (CONV == 3) L.template store<G, true>(buf(kt) + STAGE_A, 0, BN, kg, kend_f, tid_b, km);
+    else L.template store<G>(buf(kt) + STAGE_A, n0, g.N, kg, kend_f, tid_b);
   };
   const BoolTag<false> plain{};
   const BoolTag<true> guarded{};
@@ -575,8 +593,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   if (nkf > 0) {
     issueA(la[0], 0, plain);
     issueB(lb[0], 0, plain);
-    la[0].store(buf(0), tid);
-    lb[0].store(buf(0) + STAGE_A, tid_b);
+    storeA(la[0], 0, plain);
+    storeB(lb[0], 0, plain);
     if constexpr (NSTAGE == 2) {
       issueA(la[NSTAGE - 1], 1, plain);
       issueB(lb[NSTAGE - 1], 1, plain);
@@ -588,32 +606,32 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
         issueA(la[0], kt + 2, plain);
         issueB(lb[0], kt + 2, plain);
         compute(kt);
-        la[NSTAGE - 1].store(buf(kt + 1), tid);
-        lb[NSTAGE - 1].store(buf(kt + 1) + STAGE_A, tid_b);
+        storeA(la[NSTAGE - 1], kt + 1, plain);
+        storeB(lb[NSTAGE - 1], kt + 1, plain);
         __syncthreads();
         // step kt+1: set 0 holds tile kt+2; set 1 receives tile kt+3
         issueA(la[NSTAGE - 1], kt + 3, plain);
         issueB(lb[NSTAGE - 1], kt + 3, plain);
         compute(kt + 1);
-        la[0].store(buf(kt + 2), tid);
-        lb[0].store(buf(kt + 2) + STAGE_A, tid_b);
+        storeA(la[0], kt + 2, plain);
+        storeB(lb[0], kt + 2, plain);
         __syncthreads();
       } else {
         issueA(la[0], kt + 1, plain);
         issueB(lb[0], kt + 1, plain);
         compute(kt);
-        la[0].store(buf(kt + 1), tid);
-        lb[0].store(buf(kt + 1) + STAGE_A, tid_b);
+        storeA(la[0], kt + 1, plain);
+        storeB(lb[0], kt + 1, plain);
         __syncthreads();
       }
     }
   }
-  if (nkf < nk) {
+  if constexpr (CONV == 0) if (nkf < nk) {
     // the other K tiles (the last one, or all of them): masked loads, one register stage
     issueA(la[0], nkf, guarded);
     issueB(lb[0], nkf, guarded);
-    la[0].store(buf(nkf), tid);
-    lb[0].store(buf(nkf) + STAGE_A, tid_b);
+    storeA(la[0], nkf, guarded);
+    storeB(lb[0], nkf, guarded);
     __syncthreads();
     for (int kt = nkf; kt < nk; ++kt) {
       const bool more = kt + 1 < nk;
@@ -623,8 +641,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
       }
       compute(kt);
       if (more) {
-        la[0].store(buf(kt + 1), tid);
-        lb[0].store(buf(kt + 1) + STAGE_A, tid_b);
+        storeA(la[0], kt + 1, guarded);
+        storeB(lb[0], kt + 1, guarded);
       }
       __syncthreads();
     }
@@ -734,20 +752,17 @@ typedef void (*KernelFn)(KArgs);
 
 struct TileCfg {
   int bm, bn, nt;
-  KernelFn fn[2][2][2];  // [bf16?][a_kc][b_kc]
+  KernelFn fn[2][3];  // [bf16?][a_kc + b_kc]: Delta_W, Delta_X, forward (a_kc only with b_kc)
 };
 
 template <int BM, int BN, int WMW, int WNW>
 constexpr TileCfg make_cfg() {
   return TileCfg{BM, BN, 64 * WMW * WNW,
-                 {{{gemm_kernel<float, BM, BN, WMW, WNW, false, false>,
-                    gemm_kernel<float, BM, BN, WMW, WNW, false, true>},
-                   {gemm_kernel<float, BM, BN, WMW, WNW, true, false>,
-                    gemm_kernel<float, BM, BN, WMW, WNW, true, true>}},
-                  {{gemm_kernel<uint16_t, BM, BN, WMW, WNW, false, false>,
-                    gemm_kernel<uint16_t, BM, BN, WMW, WNW, false, true>},
-                   {gemm_kernel<uint16_t, BM, BN, WMW, WNW, true, false>,
-                    gemm_kernel<uint16_t, BM, BN, WMW, WNW, true, true>}}}};
+                 {{gemm_kernel<float, BM, BN, WMW, WNW, false, false>, gemm_kernel<float, BM, BN, WMW, WNW, false, true>,
+                   gemm_kernel<float, BM, BN, WMW, WNW, true, true>},
+                  {gemm_kernel<uint16_t, BM, BN, WMW, WNW, false, false>,
+                   gemm_kernel<uint16_t, BM, BN, WMW, WNW, false, true>,
+                   gemm_kernel<uint16_t, BM, BN, WMW, WNW, true, true>}}};
 }
 
 const TileCfg kCfgs[] = {
@@ -1068,7 +1083,7 @@ int gemm_run(const GemmProblem &p, void *ws, size_t ws_bytes, hipStream_t s) {
   if (dw_wide_fits(p)) return run_dw_wide(p, s);
   if (dw_sgd_fits(p) && opt(IMBD_OPT_DW_GENERIC) == 0) return run_dw_sgd(p, s);
   const TileCfg &c = kCfgs[pl.cfg];
-  KernelFn fn = c.fn[p.dtype == IMBD_BF16][p.a_kc][p.b_kc];
+  KernelFn fn = c.fn[p.dtype == IMBD_BF16][(p.a_kc ? 1 : 0) + (p.b_kc ? 1 : 0)];
   const int grid = g.tiles_m * g.tiles_n * g.splits;
   {
     LaunchTimer t(p.kclass, p.layer, s);

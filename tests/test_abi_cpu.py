@@ -252,3 +252,38 @@ def test_conv_refuses_tensors_past_32_bit_elements(lib, N, H, W, narrow, wide):
     for dtype in (0, 1):
         assert lib.conv3x3_tile_fwd(N, H, W, narrow, wide, p, p, p, dtype, None) == m.IMBD_EUNSUPPORTED
         assert lib.conv3x3_tile_dgrad(N, H, W, wide, narrow, p, p, p, dtype, None) == m.IMBD_EUNSUPPORTED
+
+
+def _kernels_private_bytes(path):
+    """Private (scratch) bytes per lane of every gfx950 kernel in a library: from the metadata notes of
+    the code objects in its offload bundles."""
+    import subprocess
+    import tempfile
+    blob, found, at = open(path, "rb").read(), {}, 0
+    num = lambda p: int.from_bytes(blob[p:p + 8], "little")  # noqa: E731
+    while (at := blob.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        p = at + 32
+        for _ in range(num(at + 24)):
+            off, size, n = num(p), num(p + 8), num(p + 16)
+            ident = blob[p + 24:p + 24 + n]
+            p += 24 + n
+            if b"gfx950" not in ident or size == 0:
+                continue
+            with tempfile.NamedTemporaryFile(suffix=".co") as f:
+                f.write(blob[at + off:at + off + size])
+                f.flush()
+                text = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True,
+                                      text=True, check=True).stdout
+            found.update({k: int(v) for k, v in
+                          re.findall(r"\.name:\s+(\S+)\n.*?\.private_segment_fixed_size:\s*(\d+)", text, re.S)})
+        at += 24
+    return found
+
+
+def test_no_kernel_spills_registers(lib):
+    """Every kernel keeps its registers: none of them has scratch memory (the tiled template's 128 x 128
+    tiles are the ones at the limit)."""
+    import paper_1712_04432_amd as m
+    found = _kernels_private_bytes(os.path.join(os.path.dirname(m.__file__), "libimbd.so"))
+    assert sum("gemm_kernel" in k for k in found) >= 30
+    assert {k: v for k, v in found.items() if v} == {}
