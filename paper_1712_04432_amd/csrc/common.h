@@ -106,6 +106,7 @@ struct GemmPlan {
   int bm, bn;    // tile sizes
   int splits;    // K splits (1 = no partial sums)
   int k_split;   // K elements per split (multiple of the K tile)
+  int chain;     // K tiles per chain of sums in tiles of 64 and fewer rows (0: a split is one chain)
   size_t ws_bytes;
 };
 

@@ -232,6 +232,7 @@ struct KArgs {
   int64_t lda, ldb;
   int M, N, K;
   int k_split, splits, tiles_m, tiles_n;
+  int chain;  // K tiles that one chain of sums takes (CHAINS only)
   Epilogue epi;
   float *partial;  // [splits][sstride] of [N][ldp] rows when splits > 1
   int64_t ldp, sstride;
@@ -360,7 +361,7 @@ __device__ __forceinline__ int conv_out_row(const KArgs &g, int P) {
 // CONV selects how operands are addressed: 0 plain matrices; 1/2/3 the forward, input-
 // gradient and weight-gradient passes of a 3x3 conv tile, computed on the positions of
 // the zero-padded (H+2) x (W+2) grid so that every tap is a row shift of a dense matrix.
-template <typename T, int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, int CONV = 0>
+template <typename T, int BM, int BN, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, int CONV = 0, bool CHAINS = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
     gemm_kernel(KArgs g) {
   constexpr int NT = 64 * WAVES_M * WAVES_N;
@@ -450,6 +451,29 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // CHAINS: the sums are those of chains of `chain` K tiles, added in order: a small product
+  // left whole in K has the rounding of the splits that it would otherwise take (and their
+  // bits). A kernel of its own, as the second set of sums takes a third of the wavefronts that
+  // fit a CU from 64 x 64 bf16 tiles (3000-1003-1001 at 600 samples: 120 -> 135 us in all).
+  static_assert(!CHAINS || CONV == 0, "plain products");
+  f32x4 tot[CHAINS ? FM : 1][CHAINS ? FN : 1];
+  int next_chain = CHAINS ? g.chain : 0;
+  if constexpr (CHAINS) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto end_chain = [&]() {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        tot[i][j] += acc[i][j];
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
+
   // The K tiles run through the fast path (whole vectors from clamped addresses, no branches
   // around the loads, so the compiler's wait counts cover exactly the tile being stored; the
   // last iterations re-load the last tile instead of skipping the load, and an odd tile count
@@ -465,6 +489,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   const int nk_fast = (nkf + NSTAGE - 1) / NSTAGE * NSTAGE;
 
   auto compute = [&](int kt) {
+    if constexpr (CHAINS) {
+      if (kt == next_chain) {
+        end_chain();
+        next_chain += g.chain;
+      }
+    }
     const char *sa = smem + (kt & 1) * STAGE;
     const char *sb = sa + STAGE_A;
 #pragma unroll
@@ -649,6 +679,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, 2)
   }
   if (nk == 0) __syncthreads();
 
+  if constexpr (CHAINS) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] += tot[i][j];
+  }
+
   if (do_db) {
     // combine the TPR consecutive threads of a row (commutative pairwise adds: every
     // lane of the group gets the same bits)
@@ -752,17 +789,28 @@ typedef void (*KernelFn)(KArgs);
 
 struct TileCfg {
   int bm, bn, nt;
-  KernelFn fn[2][3];  // [bf16?][a_kc + b_kc]: Delta_W, Delta_X, forward (a_kc only with b_kc)
+  // [bf16?][a_kc + b_kc]: Delta_W, Delta_X, forward (a_kc only with b_kc); in one chain of sums
+  // and (tiles of 64 and fewer rows) in several
+  KernelFn fn[2][3], chains[2][3];
 };
+
+template <typename T, int BM, int BN, int WMW, int WNW, bool CHAINS>
+constexpr void set_fns(KernelFn (&fn)[3]) {
+  fn[0] = gemm_kernel<T, BM, BN, WMW, WNW, false, false, 0, CHAINS>;
+  fn[1] = gemm_kernel<T, BM, BN, WMW, WNW, false, true, 0, CHAINS>;
+  fn[2] = gemm_kernel<T, BM, BN, WMW, WNW, true, true, 0, CHAINS>;
+}
 
 template <int BM, int BN, int WMW, int WNW>
 constexpr TileCfg make_cfg() {
-  return TileCfg{BM, BN, 64 * WMW * WNW,
-                 {{gemm_kernel<float, BM, BN, WMW, WNW, false, false>, gemm_kernel<float, BM, BN, WMW, WNW, false, true>,
-                   gemm_kernel<float, BM, BN, WMW, WNW, true, true>},
-                  {gemm_kernel<uint16_t, BM, BN, WMW, WNW, false, false>,
-                   gemm_kernel<uint16_t, BM, BN, WMW, WNW, false, true>,
-                   gemm_kernel<uint16_t, BM, BN, WMW, WNW, true, true>}}};
+  TileCfg c{BM, BN, 64 * WMW * WNW, {}, {}};
+  set_fns<float, BM, BN, WMW, WNW, false>(c.fn[0]);
+  set_fns<uint16_t, BM, BN, WMW, WNW, false>(c.fn[1]);
+  if constexpr (BM <= 64 && BN <= 64) {
+    set_fns<float, BM, BN, WMW, WNW, true>(c.chains[0]);
+    set_fns<uint16_t, BM, BN, WMW, WNW, true>(c.chains[1]);
+  }
+  return c;
 }
 
 const TileCfg kCfgs[] = {
@@ -814,6 +862,10 @@ static GemmPlan tiled_plan(const GemmProblem &p) {
   const int bound = p.K > 0 && ltiles < 512 && ktiles >= 4
                         ? whole_k(std::max(1, std::min(cdiv(512, ltiles), ktiles >= 16 ? ktiles / 4 : ktiles / 2)))
                         : 1;
+  // The length of that many splits is the longest chain of sums, however few splits are taken
+  // below: the rounding error grows with it (784-256-128-10 at 64 samples, fp32, against 64
+  // bits: 2.3e-7 in chains of 64 and 160 k, 3.2e-7 with K = 256 and 128 in one chain).
+  pl.chain = bound > 1 ? cdiv(cdiv(p.K, bound), BK) : 0;
   auto splits_for = [&](int tiles) {
     if (ktiles < 12 || tiles >= 512) return 1;
     int most = ktiles / 4;
@@ -1059,6 +1111,7 @@ int gemm_run(const GemmProblem &p, void *ws, size_t ws_bytes, hipStream_t s) {
   g.N = p.N;
   g.K = p.K;
   g.k_split = pl.k_split;
+  g.chain = pl.chain;
   g.splits = pl.splits;
   g.tiles_m = cdiv(p.M, pl.bm);
   g.tiles_n = cdiv(p.N, pl.bn);
@@ -1083,7 +1136,11 @@ int gemm_run(const GemmProblem &p, void *ws, size_t ws_bytes, hipStream_t s) {
   if (dw_wide_fits(p)) return run_dw_wide(p, s);
   if (dw_sgd_fits(p) && opt(IMBD_OPT_DW_GENERIC) == 0) return run_dw_sgd(p, s);
   const TileCfg &c = kCfgs[pl.cfg];
-  KernelFn fn = c.fn[p.dtype == IMBD_BF16][(p.a_kc ? 1 : 0) + (p.b_kc ? 1 : 0)];
+  const int which = (p.a_kc ? 1 : 0) + (p.b_kc ? 1 : 0);
+  KernelFn fn = c.fn[p.dtype == IMBD_BF16][which];
+  // (larger tiles than 64 x 64 are only planned where their splits are no longer than a chain)
+  if (c.chains[0][0] && pl.chain > 0 && (int64_t)pl.chain * (KT_BYTES / (p.dtype == IMBD_BF16 ? 2 : 4)) < pl.k_split)
+    fn = c.chains[p.dtype == IMBD_BF16][which];
   const int grid = g.tiles_m * g.tiles_n * g.splits;
   {
     LaunchTimer t(p.kclass, p.layer, s);

@@ -631,3 +631,34 @@ def test_bias_gradient_sum_order(imbd, dev, b, dout, din):
             s = s + row
         total = total + s
     assert np.array_equal(db.cpu().numpy(), np.float32(1.0 / b) * total)
+
+
+@pytest.mark.parametrize("dtype,dout,din,b,fwd_splits,dw_splits", [
+    # K tiles of 32 (fp32) and 64 (bf16) k: 8, 4 and 11 of them in chains of two and three, 7 and 9
+    # with a ragged last one; more than 512 tiles: one chain (and 60 K tiles: splits as planned)
+    ("f32", 128, 256, 64, 4, 1), ("f32", 10, 128, 64, 2, 1), ("f32", 77, 210, 130, 3, 2),
+    ("f32", 1000, 333, 300, 4, 5), ("f32", 2100, 256, 1900, 1, 15),
+    ("bf16", 101, 513, 203, 3, 2), ("bf16", 37, 331, 450, 3, 4)])
+def test_short_products_keep_the_chains_of_their_splits(imbd, dev, dtype, dout, din, b, fwd_splits, dw_splits):
+    """A product of few K tiles is left whole in K, but its sums are those of the splits that fill the
+    chip: the bits of the same product in that many splits and their reduce."""
+    import torch
+    rng = np.random.default_rng(dout)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    w, x, dy = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(dev).to(t)
+                for s in ((dout, din), (b, din), (b, dout)))
+    code = imbd.dtype_code(t)
+
+    def both(splits):
+        with imbd.options(gemm_splits=splits):
+            ws = torch.zeros(max(16, *(imbd.mlp_local_workspace_bytes(k, code, dout, din, b) for k in (0, 1))),
+                             dtype=torch.uint8, device=dev)
+            y, dw = torch.zeros((b, dout), device=dev), torch.zeros((dout, din), device=dev)
+            imbd.mlp_local_fwd(w, x, y, 1, 1, ws=ws)
+            imbd.mlp_local_bwd(w, dy, x, dw, 1, 1, ws=ws)
+            torch.cuda.synchronize()
+        return y, dw
+
+    y, dw = both(0)
+    assert torch.equal(y, both(fwd_splits)[0])
+    assert torch.equal(dw, both(dw_splits)[1])
