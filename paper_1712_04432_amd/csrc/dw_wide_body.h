@@ -304,10 +304,23 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
     };
     uint32_t ds = ldsd, xs = ldsx;
     lds_barrier();  // B_0
-    if constexpr (DUAL) {
-      // One k-step (the whole 32-sample slab) at a time, in one set of fragments (register
-      // budget of two workgroups per CU): a fragment of the next slab is read as soon as the
-      // last MFMA on the one before it is issued. (With all of a slab's reads ahead of its
+    if (DUAL && !SGD && nsl <= 8) {
+      // Few slabs, and the store streams as much as the product takes: one k-step (the whole
+      // 32-sample slab) at a time, whose MFMAs do not wait for the next slab to land; the other
+      // workgroup's waves cover the read latency. (With the loop below, gradients of
+      // 25088-4096-4096-1000 at 256 samples 335 instead of 332 us, of a 4096 x 9216 layer at 64
+      // 30.3 instead of 29.4; past 256 samples the loop below is the faster.)
+      for (int S = 0; S < nsl; ++S) {
+        read(ds, xs, 0, dv[0], xv[0]);
+        mma(dv[0], xv[0]);
+        lds_barrier();  // B_{S+1}
+        ds = ldsd + (uint32_t)(((S + 1) % ND) * DSLOT);
+        xs = ldsx + (uint32_t)(((S + 1) % NX) * XSLOT);
+      }
+    } else if constexpr (DUAL) {
+      // One k-step at a time, in one set of fragments (register budget of two workgroups per
+      // CU): a fragment of the next slab is read as soon as the last MFMA on the one before it
+      // is issued. (With all of a slab's reads ahead of its
       // MFMAs, their latency left to the other workgroup's waves to cover, the 4096 x 25088
       // update at 512 samples took 232 us instead of 225.)
       read(ds, xs, 0, dv[0], xv[0]);
