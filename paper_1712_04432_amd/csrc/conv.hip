@@ -466,6 +466,9 @@ __global__ void __launch_bounds__(768, 1) conv_nt_kernel(CvArgs a) {
 //   WO = 2, WK = 2: 128 output channels, the two 32-position steps of each slab to two
 //     halves of the waves, whose sums are added through LDS at the end (five slabs of ring);
 //   WO = 4, WK = 1: 256 output channels, every wave both steps (three slabs).
+// Images of one to three columns (NARROW, the former layout): 64 positions touch up to 64
+// image rows, so an activation slab has up to 192 rows in a slot twice as large, and three
+// slabs fit.
 // What bounds it is the issue of the MMA waves' other instructions, which the two waves of
 // a SIMD, in step through the slab barriers, do not hide from each other. Left to them are
 // the fragment reads and ten instructions per slab for the fragments' rows; four loader
@@ -497,25 +500,31 @@ struct CwArgs {
 // 16-byte chunks, the last two unused): a transpose read of 16 consecutive rows x 16 channels
 // touches every bank twice whatever row it starts at, and a tap is an offset of 160 bytes.
 constexpr int CW_XPITCH = 160;
-constexpr int CW_XROWS = 98;
-constexpr int CW_XSLOT = 16 * 1024;
-static_assert((CW_XROWS + 3) * CW_XPITCH <= CW_XSLOT, "activation slab");
+constexpr int cw_xrows(bool narrow) { return narrow ? 192 : 98; }
+constexpr int cw_xslot(bool narrow) { return (narrow ? 32 : 16) * 1024; }
+static_assert((cw_xrows(false) + 3) * CW_XPITCH <= cw_xslot(false) && (cw_xrows(true) + 3) * CW_XPITCH <= cw_xslot(true),
+              "activation slab");
 
+// rows of a slab: 64 positions touch at most (w + 62) / w + 1 image rows
 constexpr int cw_slab_rows(int w) { return 64 + 2 * ((w + 62) / w) + 2; }
+constexpr bool cw_narrow(int w) { return cw_slab_rows(w) > cw_xrows(false); }
+static_assert(cw_slab_rows(1) <= cw_xrows(true) && cw_narrow(3) && !cw_narrow(4), "every width fits a slab");
 
 // 16-byte chunk swizzle of a Delta_Y row (128 bytes apart), to the same end.
 __device__ __forceinline__ int cw_swz(int r) { return ((r >> 1) & 3) << 1; }
 
-template <int WO, int WK>
+template <int WO, int WK, bool NARROW>
 __global__ void __launch_bounds__(768, 1) conv_wg_kernel(CwArgs a) {
   static_assert((WO == 2 && WK == 2) || (WO == 4 && WK == 1), "eight waves, two per 64-channel half");
   constexpr uint32_t OOB = 0x80000000u;
-  constexpr int DSLOT = WO * CV_QSLOT, SLOT = DSLOT + CW_XSLOT;
-  constexpr int NS = WK == 2 ? 5 : 3;
+  static_assert(!NARROW || WK == 2, "three slots fit");
+  constexpr int CW_XROWS = cw_xrows(NARROW);
+  constexpr int DSLOT = WO * CV_QSLOT, SLOT = DSLOT + cw_xslot(NARROW);
+  constexpr int NS = WK == 2 && !NARROW ? 5 : 3;
   // slabs issued ahead of the one being read: a slot is written anew two slabs after its last
   // reads were issued (they need not have landed at the barrier in between), or, with three
   // slots, after a barrier that waits for them
-  constexpr int AHEAD = WK == 2 ? NS - 2 : NS - 1;
+  constexpr int AHEAD = NS == 5 ? NS - 2 : NS - 1;
   __shared__ __attribute__((aligned(1024))) char smem[NS * SLOT];
   static_assert(NS * SLOT <= 160 * 1024, "LDS");
 
@@ -623,9 +632,10 @@ __global__ void __launch_bounds__(768, 1) conv_wg_kernel(CwArgs a) {
       const i32x4 rx = buf_rsrc(a.x, a.x_bytes);
       const uint32_t x2 = (uint32_t)(a.Ci * 2);
       auto row = [&](int q) { return (64 * (w2 + 2 * q) + lane) / 10; };
-      uint32_t base[8];
+      constexpr int QX = NARROW ? 15 : 8;
+      uint32_t base[QX];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < QX; ++q) {
         const int c = 64 * (w2 + 2 * q) + lane - 10 * row(q);
         // (OOB plus any row's offset stays past the buffer)
         base[q] = c < 8 && row(q) < CW_XROWS ? (uint32_t)(row(q) + r3 * Wp) * x2 + (uint32_t)((c0 + 8 * c) * 2) : OOB;
@@ -649,11 +659,18 @@ __global__ void __launch_bounds__(768, 1) conv_wg_kernel(CwArgs a) {
         }
         next();
       };
-      switch ((a.xblk + 1 - w2) / 2) {  // 11 to 16 blocks
-        case 8: run(CvInt<8>{}, issue); break;
-        case 7: run(CvInt<7>{}, issue); break;
-        case 6: run(CvInt<6>{}, issue); break;
-        default: run(CvInt<5>{}, issue);
+      const int mine = (a.xblk + 1 - w2) / 2;  // of 11 to 16 blocks; 17, 21 or 30 of narrow images
+      if constexpr (NARROW) {
+        if (mine <= 9) run(CvInt<9>{}, issue);
+        else if (mine <= 11) run(CvInt<11>{}, issue);
+        else run(CvInt<15>{}, issue);
+      } else {
+        switch (mine) {
+          case 8: run(CvInt<8>{}, issue); break;
+          case 7: run(CvInt<7>{}, issue); break;
+          case 6: run(CvInt<6>{}, issue); break;
+          default: run(CvInt<5>{}, issue);
+        }
       }
     }
     vm_barrier<0>();  // every load landed
@@ -748,15 +765,19 @@ __global__ void __launch_bounds__(768, 1) conv_wg_kernel(CwArgs a) {
   for (int b = 0; b < 6; ++b) read_x(CvInt<0>{}, b);
   // (after the last slab the ring's next one, all zeros or spent, is read and not used)
   if constexpr (WK == 2) {
+    auto slab_barrier = [&]() {
+      if constexpr (NS == 5) asm volatile("s_barrier" : : : "memory");
+      else lds_barrier();
+    };
     next_rows();
     set_rows(CvInt<1>{}, 0);
     for (int S = 0;;) {
-      asm volatile("s_barrier" : : : "memory");  // B_{S+1}
+      slab_barrier();  // B_{S+1}
       rslot = up(rslot);
       next_rows();
       step(CvInt<1>{}, 0, 0);
       if (++S == nsl) break;
-      asm volatile("s_barrier" : : : "memory");
+      slab_barrier();
       rslot = up(rslot);
       next_rows();
       step(CvInt<0>{}, 0, 0);
@@ -873,10 +894,9 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
 bool conv_wg_fits(int N, int H, int W, int Ci, int Co, const void *x, const void *dy, const void *dw) {
   if (opt(IMBD_OPT_CONV_NT) == 0) return false;
   auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
-  // rows of an activation slab: 64 positions touch at most (W + 62) / W + 1 image rows (so
-  // images at least 4 wide); byte offsets within one buffer descriptor; short divisions
+  // byte offsets within one buffer descriptor; short divisions
   return N >= 1 && H >= 1 && W >= 1 && Co >= 64 && Co % 64 == 0 && Ci >= 64 && Ci % 64 == 0 && al(x) && al(dy) &&
-         al(dw) && cw_slab_rows(W) <= CW_XROWS && H < 32768 && W < 32768 &&
+         al(dw) && H < 32768 && W < 32768 &&
          (int64_t)N * (H + 2) * (W + 2) * (Ci > Co ? Ci : Co) * 2 < ((int64_t)1 << 31) &&
          (int64_t)9 * Ci * Co * 4 < ((int64_t)1 << 31);
 }
@@ -889,14 +909,16 @@ struct CwPlan {
 };
 // The output channels per workgroup and the K splits with the least modelled time: a slab
 // takes about 0.55 us with 128 output channels and 0.95 with 256 (measured at 32 x 56 x 56,
-// 256 -> 256: 105 us on 10 splits with the former, 108 on 21 with the latter), and the partials of every split are written and read once at about 4.5 TB/s
-// together with the reduce's launch (4 us). Only as many splits as ws_bytes holds partials of.
-CwPlan cw_best(int64_t M, int Ci, int Co, size_t ws_bytes, double *time) {
+// 256 -> 256: 105 us on 10 splits with the former, 108 on 21 with the latter; 1.0 us of a
+// narrow image: 1.2 one column wide, 0.85 three), and the partials of every split are written
+// and read once at about 4.5 TB/s together with the reduce's launch (4 us). Only as many splits
+// as ws_bytes holds partials of.
+CwPlan cw_best(int64_t M, int W, int Ci, int Co, size_t ws_bytes, double *time) {
   CwPlan best{};
   double &least = *time;
   least = 0;
   for (int wo : {2, 4}) {
-    if (wo == 4 && Co % 256 != 0) continue;
+    if (wo == 4 && (Co % 256 != 0 || cw_narrow(W))) continue;
     const int tco = (Co + 64 * wo - 1) / (64 * wo), tiles = tco * 3 * (Ci / 64);
     const int64_t slabs = (M + 63) / 64;
     const int most = (int)std::min<int64_t>(std::max(1, CV_CUS / tiles), (slabs + 3) / 4);
@@ -904,7 +926,7 @@ CwPlan cw_best(int64_t M, int Ci, int Co, size_t ws_bytes, double *time) {
       if (s > 1 && (size_t)s * (size_t)cw_split_stride(Ci, Co) * sizeof(float) > ws_bytes) break;
       const int64_t per = (slabs + s - 1) / s;
       const double rounds = (double)((tiles * s + CV_CUS - 1) / CV_CUS);
-      double t = rounds * (double)per * (wo == 2 ? 0.55 : 0.95);
+      double t = rounds * (double)per * (cw_narrow(W) ? 1.0 : wo == 2 ? 0.55 : 0.95);
       if (s > 1) t += 4.0 + 2.0 * s * Co * 9 * Ci * 4 / 4.5e6;
       if (best.splits == 0 || t < least) {
         least = t;
@@ -916,22 +938,22 @@ CwPlan cw_best(int64_t M, int Ci, int Co, size_t ws_bytes, double *time) {
 }
 // A plan within `prefer` bytes (what the tiled template's splits take) unless a larger
 // workspace is more than a tenth faster.
-CwPlan cw_plan(int64_t M, int Ci, int Co, size_t ws_bytes, size_t prefer) {
+CwPlan cw_plan(int64_t M, int W, int Ci, int Co, size_t ws_bytes, size_t prefer) {
   double t, tp;
-  const CwPlan any = cw_best(M, Ci, Co, ws_bytes, &t);
-  const CwPlan small = cw_best(M, Ci, Co, std::min(ws_bytes, prefer), &tp);
+  const CwPlan any = cw_best(M, W, Ci, Co, ws_bytes, &t);
+  const CwPlan small = cw_best(M, W, Ci, Co, std::min(ws_bytes, prefer), &tp);
   return tp <= 1.1 * t ? small : any;
 }
 }  // namespace
 
 size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co, size_t prefer) {
-  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, SIZE_MAX, prefer);
+  const CwPlan pl = cw_plan((int64_t)N * H * W, W, Ci, Co, SIZE_MAX, prefer);
   return pl.splits > 1 ? (size_t)pl.splits * (size_t)cw_split_stride(Ci, Co) * sizeof(float) : 0;
 }
 
 int run_conv_wg(int N, int H, int W, int Ci, int Co, const void *x, const void *dy_pad, float *dw, void *ws,
                 size_t ws_bytes, size_t prefer, hipStream_t s) {
-  const CwPlan pl = cw_plan((int64_t)N * H * W, Ci, Co, ws ? ws_bytes : 0, prefer);
+  const CwPlan pl = cw_plan((int64_t)N * H * W, W, Ci, Co, ws ? ws_bytes : 0, prefer);
   CwArgs a;
   a.x = reinterpret_cast<const uint16_t *>(x);
   a.dy = reinterpret_cast<const uint16_t *>(dy_pad);
@@ -955,8 +977,9 @@ int run_conv_wg(int N, int H, int W, int Ci, int Co, const void *x, const void *
   const int grid = (a.tiles * a.splits + 7) / 8 * 8;
   {
     LaunchTimer t(IMBD_K_CONV_WGRAD, 0, s);
-    if (pl.wo == 2) hipLaunchKernelGGL((conv_wg_kernel<2, 2>), dim3(grid), dim3(768), 0, s, a);
-    else hipLaunchKernelGGL((conv_wg_kernel<4, 1>), dim3(grid), dim3(768), 0, s, a);
+    if (cw_narrow(W)) hipLaunchKernelGGL((conv_wg_kernel<2, 2, true>), dim3(grid), dim3(768), 0, s, a);
+    else if (pl.wo == 2) hipLaunchKernelGGL((conv_wg_kernel<2, 2, false>), dim3(grid), dim3(768), 0, s, a);
+    else hipLaunchKernelGGL((conv_wg_kernel<4, 1, false>), dim3(grid), dim3(768), 0, s, a);
   }
   const int rc = check_launch("conv_wg");
   if (rc != IMBD_OK || pl.splits == 1) return rc;

@@ -338,3 +338,29 @@ def test_conv_wgrad_infinity_stays_in_its_rows(imbd, dev):
     assert bad[:, 2, 2, 7].all().item()
     bad[:, 2, 2, 7] = False
     assert not bad.any().item()
+
+
+@pytest.mark.parametrize("W", [1, 2, 3])
+@pytest.mark.parametrize("N,H,Ci,Co", [
+    # 64 positions within an image, across two, across many (of one row each); ranges of one slab,
+    # of several splits, and a last slab of a few positions; channel tiles half empty
+    (1, 300, 64, 64), (5, 31, 128, 256), (70, 1, 64, 128), (33, 5, 192, 320), (1, 2, 64, 64), (9, 64, 256, 256)])
+def test_conv_wgrad_narrow_images(imbd, dev, N, H, W, Ci, Co):
+    """The weight gradient of images one to three columns wide, whose activation slabs have up to
+    three rows per position: against the oracle and the tiled template."""
+    import torch
+    _flush(f"conv wgrad narrow {(N, H, W, Ci, Co)}")
+    d = make_conv_inputs(N, H, W, Ci, Co, seed=N + H + W)
+    x, dy = dev_bf16_bits(d["x_bits"], dev), dev_bf16_bits(d["dy_bits"], dev)
+    got = {}
+    for nt in (0, 1):
+        with imbd.options(conv_nt=nt):
+            n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
+            dw = torch.full((Co, 3, 3, Ci), float("nan"), device=dev)
+            imbd.conv3x3_tile_wgrad(x, dy, dw, ws=torch.empty(max(n, 16), dtype=torch.uint8, device=dev))
+            torch.cuda.synchronize()
+            got[nt] = host(dw)
+    assert nrm_err(got[1], got[0]) < 1e-5
+    idx = np.random.default_rng(W).integers(0, got[1].size, 60)
+    at = oracle.conv3x3_wgrad_at(bf16_values(d["x_bits"]), bf16_values(d["dy_bits"]), idx)
+    assert np.abs(got[1].reshape(-1)[idx] - at).max() < 1e-5 * np.abs(got[1]).max()
