@@ -894,6 +894,13 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
 bool conv_wg_fits(int N, int H, int W, int Ci, int Co, const void *x, const void *dy, const void *dw) {
   if (opt(IMBD_OPT_CONV_NT) == 0) return false;
   auto al = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) % 16) == 0; };
+  // Up to three of the template's K tiles (64 positions of the padded grid) on its 64 x 64 tiles
+  // (a channel count off 128), where those are all in flight at once: the template's chain is
+  // the shorter (1 x 7 x 7, 64 -> 256: 7.0 us, here 10.1; three K tiles, 1 x 11 x 11: 9.0 and
+  // 10.3; four, 1 x 13 x 13: 10.1 and 10.4, 512 -> 64 10.2 and 9.2. On its 128 x 128 tiles
+  // 1 x 7 x 7, 128 -> 256 takes 11.6, here 10.4).
+  const int64_t grid = (int64_t)(N - 1) * (H + 2) * (W + 2) + (int64_t)(H - 1) * (W + 2) + W;
+  if (grid <= 3 * 64 && (Ci % 128 != 0 || Co % 128 != 0) && (int64_t)9 * (Ci / 64) * (Co / 64) <= 512) return false;
   // byte offsets within one buffer descriptor; short divisions
   return N >= 1 && H >= 1 && W >= 1 && Co >= 64 && Co % 64 == 0 && Ci >= 64 && Ci % 64 == 0 && al(x) && al(dy) &&
          al(dw) && H < 32768 && W < 32768 &&

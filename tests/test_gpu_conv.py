@@ -364,3 +364,27 @@ def test_conv_wgrad_narrow_images(imbd, dev, N, H, W, Ci, Co):
     idx = np.random.default_rng(W).integers(0, got[1].size, 60)
     at = oracle.conv3x3_wgrad_at(bf16_values(d["x_bits"]), bf16_values(d["dy_bits"]), idx)
     assert np.abs(got[1].reshape(-1)[idx] - at).max() < 1e-5 * np.abs(got[1]).max()
+
+
+@pytest.mark.parametrize("N,H,W,Ci,Co,large", [
+    # 3 K tiles of the padded grid, and 4; one row; the narrow layout's range
+    (1, 11, 11, 64, 128, False), (3, 6, 6, 192, 64, False), (1, 1, 192, 64, 64, False), (1, 1, 193, 64, 64, True),
+    (1, 13, 13, 64, 128, True), (1, 64, 1, 64, 64, False), (1, 65, 1, 64, 64, True),
+    # both channel counts multiples of 128; more than 512 tiles of 64 x 64
+    (1, 7, 7, 128, 128, True), (1, 7, 7, 576, 448, True)])
+def test_conv_wgrad_few_positions(imbd, dev, N, H, W, Ci, Co, large):
+    """Weight gradients of few positions, at the edges of the rule that leaves them to the tiled
+    template: right on both kernels, and the one that runs is the one with its bits."""
+    import torch
+    d = make_conv_inputs(N, H, W, Ci, Co, seed=W)
+    x, dy = dev_bf16_bits(d["x_bits"], dev), dev_bf16_bits(d["dy_bits"], dev)
+    ref = oracle.conv3x3_wgrad(bf16_values(d["x_bits"]), bf16_values(d["dy_bits"]))
+    got = []
+    for nt in (0, 1):
+        with imbd.options(conv_nt=nt):
+            n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
+            got.append(torch.full((Co, 3, 3, Ci), float("nan"), device=dev))
+            imbd.conv3x3_tile_wgrad(x, dy, got[-1], ws=torch.empty(max(n, 16), dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    assert nrm_err(host(got[0]), ref) < 1e-5 and nrm_err(host(got[1]), ref) < 1e-5
+    assert torch.equal(*got) == (not large)
