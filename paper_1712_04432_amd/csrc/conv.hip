@@ -91,7 +91,9 @@ template <int V>
 struct CvInt {
   static constexpr int value = V;
 };
-// x / d for 0 <= x < 2^16 (inv = 1 / d): the half keeps the quotient's error away from whole numbers
+// x / d for 0 <= x < 2^22 (inv = 1 / d, rounded): the half keeps the quotient 0.5 / d away from
+// whole numbers, its two roundings move it by less than (x / d) 2^-23
+constexpr int CV_SIDE_MAX = 1 << 21;  // image rows and columns of the kernels, which add a tile's to them
 __device__ __forceinline__ int cv_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
 // TR: input gradient (W read transposed); else forward.
@@ -706,15 +708,15 @@ __global__ void __launch_bounds__(768, 1) conv_wg_kernel(CwArgs a) {
   uint32_t aslot = lds0;
   int aw0 = klo % a.W, acnt = kend - klo;
   uint32_t ax[2][2];  // activation fragments: set, half of the lane's k
-  const float Rq = ((float)R + 0.5f) * invw, Q16 = 16.0f * invw;
+  const float Rf = (float)R + 0.5f, Q16 = 16.0f * invw;
   const uint32_t xlane = (uint32_t)(DSLOT + 8 * (lane & 3) + 64 * wc);
   auto set_rows = [&](auto settag, int k) {
     constexpr int set = decltype(settag)::value;
-    const float q = Rq + (float)aw0 * invw;
+    const float x = Rf + (float)aw0;  // exact
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int j = R + 32 * k + 16 * h;
-      int u = j + 2 * (int)(q + (float)(2 * k + h) * Q16);
+      int u = j + 2 * (int)__builtin_fmaf(x, invw, (float)(2 * k + h) * Q16);  // (x + 16 (2k + h)) / W
       if (acnt < 64 && j >= acnt) u = CW_XROWS;  // past the range: a zero row
       ax[set][h] = (uint32_t)__umul24((uint32_t)u, CW_XPITCH) + (aslot + xlane);
       asm volatile("" : "+v"(ax[set][h]));  // worked out here, not where it is first used
@@ -887,7 +889,7 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
       !(Cn == 256 && (P + 2 * (W + 2) + 130) * Ck * 2 < ((int64_t)1 << 31)))
     return false;
   return (pass == 1 || pass == 2) && N >= 1 && H >= 1 && W >= 1 && Cn >= 64 && Cn % 64 == 0 && Ck >= 64 &&
-         Ck % 64 == 0 && al(act) && al(w) && al(out) && H < 32768 && W < 32768 && P * Ck * 2 < ((int64_t)1 << 31) &&
+         Ck % 64 == 0 && al(act) && al(w) && al(out) && H < CV_SIDE_MAX && W < CV_SIDE_MAX && P * Ck * 2 < ((int64_t)1 << 31) &&
          (int64_t)9 * Ci * Co * 2 < ((int64_t)1 << 31);
 }
 
@@ -903,7 +905,7 @@ bool conv_wg_fits(int N, int H, int W, int Ci, int Co, const void *x, const void
   if (grid <= 3 * 64 && (Ci % 128 != 0 || Co % 128 != 0) && (int64_t)9 * (Ci / 64) * (Co / 64) <= 512) return false;
   // byte offsets within one buffer descriptor; short divisions
   return N >= 1 && H >= 1 && W >= 1 && Co >= 64 && Co % 64 == 0 && Ci >= 64 && Ci % 64 == 0 && al(x) && al(dy) &&
-         al(dw) && H < 32768 && W < 32768 &&
+         al(dw) && H < CV_SIDE_MAX && W < CV_SIDE_MAX &&
          (int64_t)N * (H + 2) * (W + 2) * (Ci > Co ? Ci : Co) * 2 < ((int64_t)1 << 31) &&
          (int64_t)9 * Ci * Co * 4 < ((int64_t)1 << 31);
 }

@@ -388,3 +388,35 @@ def test_conv_wgrad_few_positions(imbd, dev, N, H, W, Ci, Co, large):
     torch.cuda.synchronize()
     assert nrm_err(host(got[0]), ref) < 1e-5 and nrm_err(host(got[1]), ref) < 1e-5
     assert torch.equal(*got) == (not large)
+
+
+@pytest.mark.parametrize("N,H,W,Ci,Co", [(1, 1, 40000, 64, 256), (2, 33000, 1, 64, 64), (1, 40001, 2, 128, 64),
+                                         (1, 2, 70001, 64, 128), (1, 300001, 1, 64, 64), (1, 1, 500000, 64, 64)])
+def test_conv_long_images(imbd, dev, N, H, W, Ci, Co):
+    """Images of more than 32768 rows or columns on the large-tile kernels: every weight gradient near
+    the template's, and outputs of the first, the last and random positions."""
+    import torch
+    _flush(f"conv long {(N, H, W, Ci, Co)}")
+    g = torch.Generator(device=dev)
+    g.manual_seed(W)
+    x = torch.randn(N, H + 2, W + 2, Ci, generator=g, device=dev).to(torch.bfloat16)
+    dy = torch.randn(N, H + 2, W + 2, Co, generator=g, device=dev).to(torch.bfloat16)
+    w = torch.randn(Co, 3, 3, Ci, generator=g, device=dev).to(torch.bfloat16)
+    out = {}
+    for nt in (0, 1):
+        with imbd.options(conv_nt=nt):
+            y, dx = torch.zeros(N, H, W, Co, device=dev), torch.zeros(N, H, W, Ci, device=dev)
+            dw = torch.zeros(Co, 3, 3, Ci, device=dev)
+            n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
+            imbd.conv3x3_tile_fwd(x, w, y)
+            imbd.conv3x3_tile_bwd(x, w, dy, dw, dx=dx, ws=torch.empty(max(n, 16), dtype=torch.uint8, device=dev))
+            torch.cuda.synchronize()
+            out[nt] = (y, dx, dw)
+    # both sum 9 C products (or all positions) of unit variance in fp32, in different orders
+    for a, b, k in zip(out[0], out[1], (9 * Ci, 9 * Co, N * H * W)):
+        assert (a - b).abs().max().item() < 1e-5 * k ** 0.5
+    pos = np.unique(np.concatenate([[0, N * H * W - 1], np.random.default_rng(W).integers(0, N * H * W, 20)]))
+    for q in pos:
+        n, h, c = q // (H * W), q // W % H, q % W
+        ref = (x[n, h:h + 3, c:c + 3].double().reshape(-1) @ w.double().reshape(Co, -1).t())
+        assert (out[1][0][n, h, c].double() - ref).abs().max().item() < 1e-5 * (9 * Ci) ** 0.5
