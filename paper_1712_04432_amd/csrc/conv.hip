@@ -43,7 +43,7 @@
 // to LDS in whole 128-byte lines, XOR-swizzled in 16-byte chunks; one barrier per slab:
 //  * waves 8-9 stream the activation slabs (one per kernel row and 64-channel chunk)
 //    through two slots, a whole slab ahead;
-//  * waves 10-11 stream the weight slabs (BN channels x 64 k of one tap) through five
+//  * waves 10-11 stream the weight slabs (BN channels x 64 k of one tap) through five (four)
 //    slots: rows of W for the forward pass, k-rows of W (64 output channels of one tap x
 //    BN input channels, in 64-channel quarters) for the input gradient, whose fragments
 //    then come from the gfx950 LDS transpose read.
@@ -63,7 +63,6 @@
 namespace imbd {
 namespace {
 
-constexpr int CV_NW = 5;               // weight ring slots
 constexpr int CV_QSLOT = 64 * 128;     // one 64-channel quarter of a transposed weight slab
 constexpr int CV_CUS = 256;            // compute units of the chip: one workgroup each
 constexpr int CV_XBUF = 32 * 1024;     // exchange of the two k halves' sums
@@ -83,7 +82,10 @@ struct CvArgs {
 
 // Rows of an activation slab in LDS: the image rows' pieces of the tile one after another,
 // each with two columns more than the tile has positions in it.
-constexpr int cv_slab_rows(int wp) { return wp == 4 ? 304 : 160; }
+// NARROW (images of few columns, whose tiles touch many image rows): more of them, and four
+// weight slots instead of five.
+constexpr int cv_slab_rows(int wp, bool narrow = false) { return narrow ? 384 : wp == 4 ? 304 : 160; }
+constexpr int cv_weight_slots(bool narrow) { return narrow ? 4 : 5; }
 
 __device__ __forceinline__ int cv_swz_kc(int r) { return r & 7; }
 __device__ __forceinline__ int cv_swz_tr(int r) { return 2 * ((r >> 1) & 1) + 4 * ((r >> 3) & 1); }
@@ -97,11 +99,11 @@ constexpr int CV_SIDE_MAX = 1 << 21;  // image rows and columns of the kernels, 
 __device__ __forceinline__ int cv_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
 // TR: input gradient (W read transposed); else forward.
-template <bool TR, int WP, int WK>
+template <bool TR, int WP, int WK, bool NARROW = false>
 __global__ void __launch_bounds__(768, 1) conv_nt_kernel(CvArgs a) {
   constexpr int WC = 8 / (WP * WK);
   constexpr int BN = 64 * WC;
-  constexpr int RA = cv_slab_rows(WP);
+  constexpr int RA = cv_slab_rows(WP, NARROW), CV_NW = cv_weight_slots(NARROW);
   constexpr uint32_t OOB = 0x80000000u;
   constexpr int WSLOT = BN * 128, ASLOT = RA * 128;
   constexpr int WRING = CV_NW * WSLOT, ARING = 2 * ASLOT;
@@ -1028,15 +1030,25 @@ int run_conv_nt(int pass, int N, int H, int W, int Ci, int Co, const void *act, 
   const bool tall = narrow || share > 8 || o >= 2;
   // blocks per tile: what the MMA waves hold and what the activation slab's rows allow (a
   // tile of n positions touches at most (W - 1 + n - 1) / W + 1 image rows)
-  const int cap = cv_slab_rows(tall ? 4 : 2);
-  a.tmax = tall ? 16 : 8;
-  if (o >= 2) a.tmax = o == 2 ? 8 : 7;
-  while (a.tmax > 1 && 16 * a.tmax + 2 * ((W + 16 * a.tmax - 2) / W) + 2 > cap) --a.tmax;
+  const int most = o == 2 ? 8 : o == 3 ? 7 : tall ? 16 : 8;
+  auto tile_max = [&](int cap) {
+    int t = most;
+    while (t > 1 && 16 * t + 2 * ((W + 16 * t - 2) / W) + 2 > cap) --t;
+    return t;
+  };
+  a.tmax = tile_max(cv_slab_rows(tall ? 4 : 2));
+  // the larger slabs where a share then takes fewer tiles: each tile of 128 channels streams all
+  // of its weights anew (32 x 224 x 4, 256 -> 256, shares of 14 blocks, forward / input gradient:
+  // 41.5 / 44.3 us in two tiles, 35.6 / 39.2 in one)
+  const int tn = tile_max(cv_slab_rows(4, true));
+  const bool few_columns = tall && !narrow && (share + tn - 1) / tn < (share + a.tmax - 1) / a.tmax;
+  if (few_columns) a.tmax = tn;
   const int grid = (a.groups * a.nct + 7) / 8 * 8;
   {
     LaunchTimer t(pass == 1 ? IMBD_K_CONV_FWD : IMBD_K_CONV_DGRAD, 0, s);
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(768), 0, s, a); };
     if (narrow) pass == 1 ? go(conv_nt_kernel<false, 4, 2>) : go(conv_nt_kernel<true, 4, 2>);
+    else if (few_columns) pass == 1 ? go(conv_nt_kernel<false, 4, 1, true>) : go(conv_nt_kernel<true, 4, 1, true>);
     else if (tall) pass == 1 ? go(conv_nt_kernel<false, 4, 1>) : go(conv_nt_kernel<true, 4, 1>);
     else pass == 1 ? go(conv_nt_kernel<false, 2, 2>) : go(conv_nt_kernel<true, 2, 2>);
   }

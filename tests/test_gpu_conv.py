@@ -420,3 +420,34 @@ def test_conv_long_images(imbd, dev, N, H, W, Ci, Co):
         n, h, c = q // (H * W), q // W % H, q % W
         ref = (x[n, h:h + 3, c:c + 3].double().reshape(-1) @ w.double().reshape(Co, -1).t())
         assert (out[1][0][n, h, c].double() - ref).abs().max().item() < 1e-5 * (9 * Ci) ** 0.5
+
+
+@pytest.mark.parametrize("N,H,W,Ci,Co", [
+    # shares of 14 blocks: one tile in the larger activation slabs (384 rows), two in the others;
+    # of 12 and 13 blocks of three and two columns; of 22 of one column, three tiles and four;
+    # 11 columns, where 14 blocks fit either way
+    (32, 224, 4, 64, 256), (40, 200, 3, 64, 256), (34, 390, 2, 64, 256), (9, 5003, 1, 64, 256), (23, 111, 11, 64, 256)])
+def test_conv_tile_few_columns(imbd, dev, N, H, W, Ci, Co):
+    """Forward and input gradient of many positions in images of few columns: the bits of the same
+    sums (in the same order) in smaller tiles."""
+    import torch
+    _flush(f"conv few columns {(N, H, W, Ci, Co)}")
+    g = torch.Generator(device=dev)
+    g.manual_seed(W)
+    x = torch.randn(N, H + 2, W + 2, Ci, generator=g, device=dev).to(torch.bfloat16)
+    dy = torch.randn(N, H + 2, W + 2, Co, generator=g, device=dev).to(torch.bfloat16)
+    w = torch.randn(Co, 3, 3, Ci, generator=g, device=dev).to(torch.bfloat16)
+    out = []
+    for nt in (1, 3):
+        with imbd.options(conv_nt=nt):
+            out.append([torch.full((N, H, W, c), float("nan"), device=dev) for c in (Co, Ci)])
+            imbd.conv3x3_tile_fwd(x, w, out[-1][0])
+            imbd.conv3x3_tile_dgrad(dy, w, out[-1][1])
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    for q in np.unique(np.concatenate([[0, N * H * W - 1], np.random.default_rng(W).integers(0, N * H * W, 40)])):
+        n, h, c = q // (H * W), q // W % H, q % W
+        y = x[n, h:h + 3, c:c + 3].double().reshape(-1) @ w.double().reshape(Co, -1).t()
+        dx = dy[n, h:h + 3, c:c + 3].flip(0, 1).double().reshape(-1) @ w.double().permute(1, 2, 0, 3).reshape(-1, Ci)
+        assert (out[0][0][n, h, c].double() - y).abs().max().item() < 1e-5 * (9 * Ci) ** 0.5
+        assert (out[0][1][n, h, c].double() - dx).abs().max().item() < 1e-5 * (9 * Co) ** 0.5
