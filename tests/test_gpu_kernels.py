@@ -480,13 +480,21 @@ def test_skinny_every_plan(imbd, dev, nb, splits, shape):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [
     # d_out, d_in, b: widths below one vector; K tails of 1..7 in the one K tile and after many;
-    # tiles of 32, 64 and 128 with ragged rows; split K with a ragged last split
+    # ragged rows of every tile size; split K with a ragged last split
     (5, 7, 3), (9, 33, 17), (37, 101, 13), (130, 203, 70), (517, 1023, 200), (258, 4099, 131), (1031, 259, 263)])
-def test_unaligned_blocks_in_nan_surroundings(imbd, dev, dtype, shape):
+@pytest.mark.parametrize("plan", [{}, {"gemm_cfg": 0}, {"gemm_cfg": 1}, {"gemm_cfg": 2}, {"gemm_cfg": 3}, {"gemm_cfg": 4},
+                                  {"gemm_cfg": 1, "gemm_splits": 3}, {"gemm_cfg": 4, "gemm_splits": 3}])
+def test_unaligned_blocks_in_nan_surroundings(imbd, dev, dtype, shape, plan):
     """Blocks that start at an odd element of arrays with an odd pitch, everything outside them NaN:
     the tiled template's whole-vector loads at any address, its reads past a ragged row (into
     the next one) and its ragged last K tile must let none of it into an output, and nothing
-    outside the output blocks may be written."""
+    outside the output blocks may be written. As planned (tiles of 32 and 64 rows at these sizes)
+    and on every tile configuration (64 x 64, 128 x 128, 128 x 64, 64 x 128, 32 x 32)."""
+    with imbd.options(**plan):
+        _unaligned_blocks(imbd, dev, dtype, shape)
+
+
+def _unaligned_blocks(imbd, dev, dtype, shape):
     import torch
     dout, din, b = shape
     _flush(f"unaligned {dtype} {shape}")
