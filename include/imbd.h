@@ -227,7 +227,11 @@ int conv3x3_tile_dgrad(int N, int H, int W, int C_in, int C_out, const void *dy_
 
 /* The tile's partial weight gradient (the all-reduce over all processes of Eq. (7)
  * completes it): dw[o][r][s][c] = sum_{n,h,w} dy[n][h][w][o] x_pad[n][h+r][w+s][c],
- * dy = interior of dy_pad; dw [C_out][3][3][C_in] fp32. */
+ * dy = interior of dy_pad; dw [C_out][3][3][C_in] fp32. ws (16-byte aligned) holds the partial
+ * sums of ranges of the positions. conv3x3_wgrad_workspace_bytes is the size to bring: from it
+ * on, the ranges, and so the order of the sums and dw's bits, are the same. Some shapes accept
+ * less, down to none (IMBD_EWORKSPACE below the least): dw is then summed over fewer ranges,
+ * more slowly and in another order. */
 int conv3x3_tile_wgrad(int N, int H, int W, int C_in, int C_out, const void *x_pad,
                        const void *dy_pad, float *dw, void *ws, size_t ws_bytes, void *stream);
 size_t conv3x3_wgrad_workspace_bytes(int N, int H, int W, int C_in, int C_out);
@@ -235,7 +239,7 @@ size_t conv3x3_wgrad_workspace_bytes(int N, int H, int W, int C_in, int C_out);
 /* The tile's whole backward pass (Sec. 2.2; Eq. (7) for what it exchanges): the input
  * gradient (as conv3x3_tile_dgrad, skipped when dx is NULL) and the partial weight
  * gradient (as conv3x3_tile_wgrad), on `stream` in that order. Both passes are validated
- * before either is enqueued; ws must hold conv3x3_wgrad_workspace_bytes. */
+ * before either is enqueued; ws as for conv3x3_tile_wgrad. */
 int conv3x3_tile_bwd(int N, int H, int W, int C_in, int C_out, const void *x_pad, const void *w,
                      const void *dy_pad, void *dx, int dx_dtype, float *dw, void *ws,
                      size_t ws_bytes, void *stream);

@@ -692,8 +692,8 @@ int conv3x3_tile_bwd(int N, int H, int W, int C_in, int C_out, const void *x_pad
   if (dx && !valid_dtype(dx_dtype)) FAIL(IMBD_EINVAL, "unknown dx dtype");
   if (!dw) FAIL(IMBD_EINVAL, "dw must be set");
   if (N > 0 && (!x_pad || !dy_pad || (dx && !w))) FAIL(IMBD_EINVAL, "x_pad, dy_pad (and w with dx) must be set");
-  if (N > 0 && ws_bytes < conv_wgrad_ws_least(N, H, W, C_in, C_out))
-    FAIL(IMBD_EWORKSPACE, "workspace has %zu bytes, need %zu", ws_bytes, conv_wgrad_ws_least(N, H, W, C_in, C_out));
+  if (const size_t least = conv_wgrad_ws_least(N, H, W, C_in, C_out, true); N > 0 && ws_bytes < least)
+    FAIL(IMBD_EWORKSPACE, "workspace has %zu bytes, need %zu", ws_bytes, least);
   if (dx) TRY(conv3x3_tile_dgrad(N, H, W, C_in, C_out, dy_pad, w, dx, dx_dtype, stream));
   return conv3x3_tile_wgrad(N, H, W, C_in, C_out, x_pad, dy_pad, dw, ws, ws_bytes, stream);
 }

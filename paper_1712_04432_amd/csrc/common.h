@@ -231,9 +231,10 @@ int run_conv_dgrad(int N, int H, int W, int Ci, int Co, const void *dyp, const v
                    int dx_dtype, hipStream_t s);
 int run_conv_wgrad(int N, int H, int W, int Ci, int Co, const void *xp, const void *dyp,
                    float *dw, void *ws, size_t ws_bytes, hipStream_t s);
-// Workspace for the planned K splits, and the least that a call accepts (fewer splits then).
+// Workspace for the planned K splits, and the least that a call accepts, the weight gradient by
+// itself or (bwd) the whole backward pass: fewer splits then.
 size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co);
-size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co);
+size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co, bool bwd);
 // The forward (pass 1) and input-gradient (pass 2) passes on the large-tile implicit-GEMM
 // kernel (channel counts that are multiples of 64): whether it takes the problem, and the launch.
 bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act, const void *w, const void *out);

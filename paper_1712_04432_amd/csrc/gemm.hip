@@ -1196,20 +1196,26 @@ ConvPlan conv_plan(int pass, int N, int H, int W, int Ci, int Co) {
 }
 }  // namespace
 
-size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co) {
-  if (Ci % 64 || Co % 64) return 0;
-  size_t b = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
-  if (N >= 1 && conv_wg_fits(N, H, W, Ci, Co, nullptr, nullptr, nullptr)) {
-    // the large-tile kernel's split partials
-    const size_t w = conv_wg_ws_bytes(N, H, W, Ci, Co, b);
-    if (w > b) b = w;
-  }
-  return b;
+// The partials of as many ranges of positions as 256 workgroups of 256 x 128 outputs make: enough
+// for a weight gradient with 256 output channels (C_in a multiple of 128), as it always was.
+static size_t conv_wgrad_256_bytes(int N, int H, int W, int Ci, int Co) {
+  const int64_t rows = (int64_t)N * (H + 2) * (W + 2) + 2 * (W + 2) + 2 + 64, M = (int64_t)N * H * W;
+  if (opt(IMBD_OPT_CONV_NT) == 0 || Co != 256 || Ci % 128 || rows * std::max(Ci, Co) * 2 >= ((int64_t)1 << 31)) return 0;
+  const int64_t s = std::max(1, 256 / (9 * Ci / 128)), per = std::max<int64_t>(64, ((M + s - 1) / s + 63) / 64 * 64);
+  return (size_t)((M + per - 1) / per) * (size_t)partial_split_stride(9 * Ci, Co) * sizeof(float);
 }
 
-size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co) {
+size_t conv_wgrad_ws_least(int N, int H, int W, int Ci, int Co, bool bwd) {
   if (Ci % 64 || Co % 64 || N < 1) return 0;
-  return conv_plan(3, N, H, W, Ci, Co).ws_bytes;
+  const size_t t = conv_plan(3, N, H, W, Ci, Co).ws_bytes, w = conv_wgrad_256_bytes(N, H, W, Ci, Co);
+  return !bwd && w > 0 ? std::min(t, w) : t;
+}
+
+size_t conv_wgrad_ws_bytes(int N, int H, int W, int Ci, int Co) {
+  if (Ci % 64 || Co % 64) return 0;
+  const size_t t = conv_plan(3, N, H, W, Ci, Co).ws_bytes;
+  if (N < 1 || !conv_wg_fits(N, H, W, Ci, Co, nullptr, nullptr, nullptr)) return t;
+  return std::max(t, conv_wg_ws_bytes(N, H, W, Ci, Co, t));  // the large-tile kernel's split partials
 }
 
 static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void *A, const void *B, void *out,
@@ -1221,9 +1227,8 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
   if (pass != 3 && conv_nt_fits(pass, N, H, W, Ci, Co, B, A, out))
     return run_conv_nt(pass, N, H, W, Ci, Co, B, A, out, out_dtype, s);
   if (pass == 3) {
-    // the template's partials are the least that a call has to bring; the large-tile kernel
-    // takes as many splits as fit into what it is given
-    const size_t least = conv_wgrad_ws_least(N, H, W, Ci, Co);
+    // (the large-tile kernel takes as many splits as fit into what it is given)
+    const size_t least = conv_wgrad_ws_least(N, H, W, Ci, Co, false);
     if (least > 0 && (ws == nullptr || ws_bytes < least || (uintptr_t)ws % 16)) {
       set_error("conv weight gradient needs %zu bytes of 16-byte aligned workspace, got %zu", least, ws_bytes);
       return IMBD_EWORKSPACE;
@@ -1235,7 +1240,7 @@ static int conv_launch(int pass, int N, int H, int W, int Ci, int Co, const void
   }
   if (pass == 3 && conv_wg_fits(N, H, W, Ci, Co, A, B, out))
     return run_conv_wg(N, H, W, Ci, Co, A, B, reinterpret_cast<float *>(out), ws, ws_bytes,
-                       conv_wgrad_ws_least(N, H, W, Ci, Co), s);
+                       conv_plan(3, N, H, W, Ci, Co).ws_bytes, s);
   const ConvPlan pl = conv_plan(pass, N, H, W, Ci, Co);
   if ((int64_t)N * (H + 2) * (W + 2) * (Ci > Co ? Ci : Co) >= ((int64_t)1 << 31)) {
     set_error("conv tile too large for 32-bit element offsets");

@@ -298,28 +298,58 @@ def test_conv_tile_every_channel_count_sampled(imbd, dev, N, H, W, Ci, Co, out_b
     assert torch.isfinite(dw).all().item()
 
 
-@pytest.mark.parametrize("N,H,W,Ci,Co", [(3, 20, 20, 64, 256), (2, 9, 3, 64, 64), (5, 31, 17, 128, 384)])
-def test_conv_wgrad_splits_that_fit(imbd, dev, N, H, W, Ci, Co):
-    """The weight gradient with the workspace that its size query names, with half of that (fewer
-    K splits) and, where that is accepted, with none (one range that writes dW itself)."""
+@pytest.mark.parametrize("N,H,W,Ci,Co,planned", [
+    # nothing has to be brought, and the plan takes this many K splits
+    (1, 30, 30, 64, 64, 4), (1, 40, 22, 64, 128, 4), (1, 25, 35, 64, 64, 4)])
+def test_conv_wgrad_splits_that_fit(imbd, dev, N, H, W, Ci, Co, planned):
+    """The weight gradient with the workspace that its size query names, more of it, room for three, two
+    and less than one of its K splits and none at all: each takes splits that fit (or, where those are
+    hardly faster, one range, which writes dW itself), none is refused, and from the queried size
+    on the bits stay the same."""
     import torch
     d = make_conv_inputs(N, H, W, Ci, Co, seed=3)
     ref = oracle.conv3x3_wgrad(bf16_values(d["x_bits"]), bf16_values(d["dy_bits"]))
     x, dy = dev_bf16_bits(d["x_bits"], dev), dev_bf16_bits(d["dy_bits"], dev)
     n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
-    taken = 0
-    for nbytes in (n, n // 2, 0):
-        dw = torch.full((Co, 3, 3, Ci), float("nan"), device=dev)
-        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev) if nbytes else None
-        try:
-            imbd.conv3x3_tile_wgrad(x, dy, dw, ws=ws)
-        except imbd.ImbdError as e:
-            assert e.status == imbd.IMBD_EWORKSPACE and nbytes < n
-            continue
+    one = (9 * Ci * Co + 1088) * 4
+    assert n == planned * one
+    got = {}
+    for nbytes in (n, 3 * n, 3 * one, 2 * one, one // 2, 0):
+        got[nbytes] = torch.full((Co, 3, 3, Ci), float("nan"), device=dev)
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device=dev) if nbytes else None
+        imbd.conv3x3_tile_wgrad(x, dy, got[nbytes], ws=ws)
         torch.cuda.synchronize()
-        taken += 1
-        assert nrm_err(host(dw), ref) < 1e-5
-    assert taken >= 1
+        assert nrm_err(host(got[nbytes]), ref) < 1e-5
+    assert torch.equal(got[n], got[3 * n]) and torch.equal(got[one // 2], got[0])
+    assert not torch.equal(got[n], got[0])  # other splits, another order of the sums
+
+
+@pytest.mark.parametrize("N,H,W,Ci,Co", [(3, 20, 20, 64, 256), (5, 31, 17, 128, 384), (9, 56, 56, 256, 256)])
+def test_conv_wgrad_least_workspace(imbd, dev, N, H, W, Ci, Co):
+    """Shapes that have to bring partial sums: the least is accepted, right and no part of it is
+    overrun, a byte less is refused. (Elsewhere than at 256 output channels and C_in a multiple of
+    128 the least is the queried size.)"""
+    import torch
+    d = make_conv_inputs(N, H, W, Ci, Co, seed=3)
+    x, dy = dev_bf16_bits(d["x_bits"], dev), dev_bf16_bits(d["dy_bits"], dev)
+    least = n = imbd.conv3x3_wgrad_workspace_bytes(N, H, W, Ci, Co)
+    if Co == 256 and Ci % 128 == 0:
+        # as many ranges as 256 workgroups of 256 x 128 outputs make
+        per = -(-(N * H * W) // (256 // (9 * Ci // 128)))
+        per = -(-per // 64) * 64
+        least = -(-(N * H * W) // per) * (Co * (9 * Ci + 64) + 1088) * 4
+        assert least < n
+    ws = torch.full((n + 4096,), 255, dtype=torch.uint8, device=dev)
+    dw = torch.full((Co, 3, 3, Ci), float("nan"), device=dev)
+    with pytest.raises(imbd.ImbdError) as e:
+        imbd.conv3x3_tile_wgrad(x, dy, dw, ws=ws[:least - 1])
+    assert e.value.status == imbd.IMBD_EWORKSPACE
+    imbd.conv3x3_tile_wgrad(x, dy, dw, ws=ws[:least])
+    torch.cuda.synchronize()
+    idx = np.random.default_rng(N).integers(0, dw.numel(), 60)
+    at = oracle.conv3x3_wgrad_at(bf16_values(d["x_bits"]), bf16_values(d["dy_bits"]), idx)
+    assert np.abs(host(dw).reshape(-1)[idx] - at).max() < 1e-5 * dw.abs().max().item()
+    assert (ws[least:] == 255).all().item()
 
 
 def test_conv_wgrad_infinity_stays_in_its_rows(imbd, dev):
