@@ -304,45 +304,18 @@ __device__ __forceinline__ void dw_wide_body(const DlArgs &a, char *smem, int bi
     };
     uint32_t ds = ldsd, xs = ldsx;
     lds_barrier();  // B_0
-    if (DUAL && !SGD && nsl <= 8) {
-      // Few slabs, and the store streams as much as the product takes: one k-step (the whole
-      // 32-sample slab) at a time, whose MFMAs do not wait for the next slab to land; the other
-      // workgroup's waves cover the read latency. (With the loop below, gradients of
-      // 25088-4096-4096-1000 at 256 samples 335 instead of 332 us, of a 4096 x 9216 layer at 64
-      // 30.3 instead of 29.4; past 256 samples the loop below is the faster.)
+    if constexpr (DUAL) {
+      // One k-step (the whole 32-sample slab) at a time (register budget of two workgroups per
+      // CU); the other workgroup's waves cover the read latency. (Fragments of the next slab read
+      // anew in place between the MFMAs, which then wait for that slab to land: the
+      // 9216-4096-4096-1000 step at 2048 samples 640 instead of 636 us, stored gradients of a
+      // 4096 x 9216 layer at 64 samples 30.4 instead of 29.4, 25088-4096-4096-1000 at 512 the same.)
       for (int S = 0; S < nsl; ++S) {
         read(ds, xs, 0, dv[0], xv[0]);
         mma(dv[0], xv[0]);
         lds_barrier();  // B_{S+1}
         ds = ldsd + (uint32_t)(((S + 1) % ND) * DSLOT);
         xs = ldsx + (uint32_t)(((S + 1) % NX) * XSLOT);
-      }
-    } else if constexpr (DUAL) {
-      // One k-step at a time, in one set of fragments (register budget of two workgroups per
-      // CU): a fragment of the next slab is read as soon as the last MFMA on the one before it
-      // is issued. (With all of a slab's reads ahead of its
-      // MFMAs, their latency left to the other workgroup's waves to cover, the 4096 x 25088
-      // update at 512 samples took 232 us instead of 225.)
-      read(ds, xs, 0, dv[0], xv[0]);
-      for (int S = 0; S < nsl; ++S) {
-        lds_barrier();  // B_{S+1}: every read of slab S has landed
-        ds = ldsd + (uint32_t)(((S + 1) % ND) * DSLOT);
-        xs = ldsx + (uint32_t)(((S + 1) % NX) * XSLOT);
-#pragma unroll
-        for (int i = 0; i < FM; ++i) {
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dv[0][i], xv[0][j], acc[i][j], 0, 0, 0);
-            if (i == FM - 1) {
-              __builtin_amdgcn_sched_barrier(0);
-              xv[0][j] = tr8(xs + fx[j]);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          dv[0][i] = tr8(ds + fa[i]);  // past the last slab a spent slot, unused
-        }
-        __builtin_amdgcn_sched_barrier(0);
       }
     } else {
       read(ds, xs, 0, dv[0], xv[0]);
