@@ -241,8 +241,7 @@ bool conv_nt_fits(int pass, int N, int H, int W, int Ci, int Co, const void *act
 int run_conv_nt(int pass, int N, int H, int W, int Ci, int Co, const void *act, const void *w, void *out,
                 int out_dtype, hipStream_t s);
 // The weight-gradient pass on the large-tile kernel (channel counts that are multiples of
-// 64): whether it takes the problem, the workspace of its K splits'
-// partials, and the launches.
+// 64): whether it takes the problem, the workspace of its K splits' partials, and the launches.
 bool conv_wg_fits(int N, int H, int W, int Ci, int Co, const void *x, const void *dy, const void *dw);
 // prefer: bytes that the plan stays within unless more splits are clearly faster.
 size_t conv_wg_ws_bytes(int N, int H, int W, int Ci, int Co, size_t prefer);
