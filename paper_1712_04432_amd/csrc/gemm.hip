@@ -1197,7 +1197,8 @@ ConvPlan conv_plan(int pass, int N, int H, int W, int Ci, int Co) {
 }  // namespace
 
 // The partials of as many ranges of positions as 256 workgroups of 256 x 128 outputs make: enough
-// for a weight gradient with 256 output channels (C_in a multiple of 128), as it always was.
+// for a weight gradient by itself with 256 output channels (C_in a multiple of 128), where the
+// template's may be more.
 static size_t conv_wgrad_256_bytes(int N, int H, int W, int Ci, int Co) {
   const int64_t rows = (int64_t)N * (H + 2) * (W + 2) + 2 * (W + 2) + 2 + 64, M = (int64_t)N * H * W;
   if (opt(IMBD_OPT_CONV_NT) == 0 || Co != 256 || Ci % 128 || rows * std::max(Ci, Co) * 2 >= ((int64_t)1 << 31)) return 0;
